@@ -41,7 +41,7 @@ def source_digest() -> str:
 # The headers that hold the forward pass's kernels (the prefill GEMM with its
 # epilogues and the decode weight streams); counters taken on one version of
 # them stay valid while these files are unchanged.
-FORWARD_KERNEL_SOURCES = ("common.hpp", "layout.hpp", "epilogue.hpp", "gemm_mfma.hpp", "gemv_skinny.hpp",
+FORWARD_KERNEL_SOURCES = ("common.hpp", "layout.hpp", "epilogue.hpp", "gemm_mfma.hpp", "gemm_dma.hpp", "gemv_skinny.hpp",
                           "prepack.hpp")
 
 

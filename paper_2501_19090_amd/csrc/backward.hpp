@@ -24,6 +24,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "epilogue.hpp"
 #include "layout.hpp"
 
 namespace pifa {
@@ -163,63 +164,121 @@ __global__ __launch_bounds__(256) void gather_tile(const bf16* __restrict__ in, 
     }
 }
 
+// Rows of in (M x d, row stride d) split by column sets: out_a[m][j] =
+// in[m][ia[j]] for j < na (zeros up to lda) and, if out_b, out_b[m][j] =
+// in[m][ib[j]] for j < nb (zeros up to ldb); lda and ldb are multiples of 8
+// and the outputs 16-byte aligned.  One workgroup takes R rows: they are read
+// once, whole lines at a time, into LDS, and the outputs gathered
+// from there, 8 columns of one index load and one 16-byte store per row.  The
+// bound is memory: for a 4096 x 4096 gradient split in halves 67 MB in 15 us,
+// where a gather of each half alone, 2 bytes per load, read every line of the
+// rows for it and took 15 us.
+// Dynamic LDS: R * round_up(d, 8) * 2 bytes.
+constexpr int kSplitRows = 2;  // R where two rows fit 64 KB
+
+__global__ __launch_bounds__(512) void split_columns(const bf16* __restrict__ in, int64_t d, int64_t M, int R,
+                                                     const int32_t* __restrict__ ia, int64_t na,
+                                                     bf16* __restrict__ out_a, int64_t lda,
+                                                     const int32_t* __restrict__ ib, int64_t nb,
+                                                     bf16* __restrict__ out_b, int64_t ldb) {
+    extern __shared__ __attribute__((aligned(16))) uint16_t rows[];
+    const int64_t m0 = (int64_t)blockIdx.x * R;
+    const int nr = (int)((M - m0) < R ? (M - m0) : R);
+    const int64_t pitch = round_up(d, (int64_t)8);
+    const uint16_t* src = reinterpret_cast<const uint16_t*>(in) + m0 * d;
+    if ((d & 7) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {
+        for (int64_t q = threadIdx.x; q < nr * d / 8; q += 512)
+            reinterpret_cast<u32x4*>(rows)[q] = reinterpret_cast<const u32x4*>(src)[q];
+    } else {
+        for (int r = 0; r < nr; ++r)
+            for (int64_t j = threadIdx.x; j < d; j += 512) rows[r * pitch + j] = src[r * d + j];
+    }
+    __syncthreads();
+    auto gather = [&](const int32_t* __restrict__ idx, int64_t n, bf16* __restrict__ out, int64_t ld) {
+        for (int64_t j = 8 * (int64_t)threadIdx.x; j < ld; j += 8 * 512) {
+            int32_t c[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) c[e] = idx[j + e < n ? j + e : n - 1];
+            for (int r = 0; r < nr; ++r) {
+                uint16_t v[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = j + e < n ? rows[r * pitch + c[e]] : (uint16_t)0;
+                store_run16<8>(reinterpret_cast<uint16_t*>(out) + (m0 + r) * ld + j, v);
+            }
+        }
+    };
+    gather(ia, na, out_a, lda);
+    if (out_b) gather(ib, nb, out_b, ldb);
+}
+
 // Epilogue of G_p = G[:, I^c] C (+ G[:, I]): acc(m, n) for n < r_pad.
-//   * the accumulator starts from G[m, piv[n]] for n < r (init);
+//   * the accumulator starts from gpi[m * r_pad + n] = G[m, piv[n]] (zeros at
+//     n >= r), the gathered pivot columns (init);
 //   * writes G_p in fp32 to gp[m * r_pad + n] (padding columns n >= r get
 //     zeros), for the row-wise fp16 conversion;
 //   * writes bf16(G_p) to gpb[m * r_pad + n] (zeros at n >= r): the K-major
 //     A operand of dW_p = G_p^T X.
-// In a whole tile the fp32 rows go out element by element (store4_rows) and
-// the bf16 rows through the staged 16-byte epilogue (staged()); the K-split
-// reduction uses store().
+// The padding columns need no mask: C^T's padding rows and their starting
+// values are zero.  gpi, gp and gpb have 16-byte aligned rows (r_pad is a
+// multiple of 64).
 struct GradPivotEpi {
     static constexpr bool kRowsPlusStaged = true;
-    const bf16* G;
-    int64_t ldg;
-    const int32_t* piv;
-    int64_t r, r_pad;
+    const bf16* gpi;
+    int64_t r_pad;
     float* gp;
     bf16* gpb;
     int64_t M;
 
     struct Col {
         int64_t n;
-        int64_t src;
-        bool piv_ok;
+        bool ok;
     };
-    // The loads below are unconditional, from clamped (valid) addresses, with
-    // the result selected afterwards: a load under a lane-dependent condition
-    // is compiled as a branch that waits for it, which serialised the 64
-    // starting-value loads of a lane (15 of the product's 63 us).
-    __device__ __forceinline__ Col col(int64_t n) const {
-        Col c;
-        c.n = n;
-        c.piv_ok = n < r;
-        const int32_t p = piv[c.piv_ok ? n : 0];
-        c.src = c.piv_ok ? (int64_t)p : 0;
-        return c;
-    }
-    // the product starts from G[m, piv[n]] (the G[:, I] term)
+    __device__ __forceinline__ Col col(int64_t n) const { return Col{n, n < r_pad}; }
+    // Loads below are unconditional, from clamped (valid) addresses: a load
+    // under a lane-dependent condition is compiled as a branch that waits for it.
     __device__ __forceinline__ float init(int64_t m, const Col& c) const {
-        const uint16_t* g16 = reinterpret_cast<const uint16_t*>(G);
-        const float g = bf16_bits_to_f32(g16[(m < M ? m : 0) * ldg + c.src]);
-        return (c.piv_ok && m < M) ? g : 0.f;
+        const uint16_t* g16 = reinterpret_cast<const uint16_t*>(gpi);
+        const float g = bf16_bits_to_f32(g16[(m < M ? m : 0) * r_pad + (c.ok ? c.n : 0)]);
+        return (c.ok && m < M) ? g : 0.f;
+    }
+    template <int W>
+    __device__ __forceinline__ void init_run(int64_t m, int64_t n, float (&v)[W]) const {
+        static_assert(W % 8 == 0, "16-byte loads");
+        const u32x4* src = reinterpret_cast<const u32x4*>(gpi + (m < M ? m : 0) * r_pad + (n + W <= r_pad ? n : 0));
+        u32x4 w[W / 8];
+#pragma unroll
+        for (int x = 0; x < W / 8; ++x) w[x] = src[x];
+        const uint32_t keep = n + W <= r_pad ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+        for (int x = 0; x < W / 2; ++x) {
+            const uint32_t u = w[x / 4][x % 4] & keep;
+            v[2 * x] = bf16_bits_to_f32((uint16_t)u);
+            v[2 * x + 1] = bf16_bits_to_f32((uint16_t)(u >> 16));
+        }
+    }
+    template <int W>
+    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
+        if (m >= M || n + W > r_pad) return;
+        f32x4* d = reinterpret_cast<f32x4*>(gp + m * r_pad + n);
+        uint16_t h[W];
+#pragma unroll
+        for (int x = 0; x < W / 4; ++x) d[x] = f32x4{v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]};
+#pragma unroll
+        for (int x = 0; x < W; ++x) h[x] = f32_to_bf16_bits(v[x]);
+        store_run16<W>(reinterpret_cast<uint16_t*>(gpb) + m * r_pad + n, h);
     }
     __device__ __forceinline__ void store(int64_t m, const Col& c, float v) const {
-        if (m >= M || c.n >= r_pad) return;
-        const float g = c.piv_ok ? v : 0.f;
-        gp[m * r_pad + c.n] = g;
-        reinterpret_cast<uint16_t*>(gpb)[m * r_pad + c.n] = f32_to_bf16_bits(g);
+        if (m >= M || !c.ok) return;
+        gp[m * r_pad + c.n] = v;
+        reinterpret_cast<uint16_t*>(gpb)[m * r_pad + c.n] = f32_to_bf16_bits(v);
     }
     // rows m .. m + 3 (m % 4 == 0) of column c, fp32 rows only
     __device__ __forceinline__ void store4_rows(int64_t m, const Col& c, const float (&v)[4]) const {
-        if (c.n >= r_pad || m >= M) return;
+        if (!c.ok || m >= M) return;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            if (m + e < M) gp[(m + e) * r_pad + c.n] = c.piv_ok ? v[e] : 0.f;
+            if (m + e < M) gp[(m + e) * r_pad + c.n] = v[e];
     }
-    // the bf16 rows (the tile's padding columns n >= r hold zero products:
-    // C^T's padding rows and their starting values are zero)
     __device__ __forceinline__ StagedEpi<bf16> staged() const {
         return StagedEpi<bf16>{reinterpret_cast<uint16_t*>(gpb), r_pad, r_pad, 1.f, nullptr, M};
     }
@@ -267,6 +326,7 @@ struct RowScaleEpi {
     const float* row_scale;
     float out_scale;
     int64_t M;
+    bool vec;  // rows of out are 16-byte aligned
     struct Col {
         int64_t n;
         bool ok;
@@ -274,6 +334,22 @@ struct RowScaleEpi {
     __device__ __forceinline__ Col col(int64_t n) const { return Col{n, n < N}; }
     __device__ __forceinline__ void store(int64_t m, const Col& c, float v) const {
         if (m < M && c.ok) Store<bf16>::put(out + m * ldo + c.n, v * row_scale[m] * out_scale);
+    }
+    template <int W>
+    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
+        if (m >= M || n >= N) return;
+        const float s = row_scale[m];
+        uint16_t h[W];
+#pragma unroll
+        for (int x = 0; x < W; ++x) h[x] = f32_to_bf16_bits(v[x] * s * out_scale);
+        uint16_t* dst = reinterpret_cast<uint16_t*>(out) + m * ldo + n;
+        if (n + W <= N && vec) {
+            store_run16<W>(dst, h);
+        } else {
+#pragma unroll
+            for (int x = 0; x < W; ++x)
+                if (n + x < N) dst[x] = h[x];
+        }
     }
     // rows m .. m + 3 (m % 4 == 0) of column c: one 16-byte load of their
     // scales (row_scale holds M rounded up to 4 values)

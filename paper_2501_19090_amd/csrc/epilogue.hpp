@@ -17,6 +17,25 @@
 
 namespace pifa {
 
+// W consecutive 16-bit values (W a multiple of 4) in the widest stores that
+// their alignment allows: p is 16-byte aligned if W is a multiple of 8, else
+// 8-byte aligned.
+template <int W>
+__device__ __forceinline__ void store_run16(uint16_t* p, const uint16_t (&h)[W]) {
+    static_assert(W % 4 == 0, "runs of 4 columns");
+    uint32_t w[W / 2];
+#pragma unroll
+    for (int x = 0; x < W / 2; ++x) w[x] = (uint32_t)h[2 * x] | ((uint32_t)h[2 * x + 1] << 16);
+    if constexpr (W % 8 == 0) {
+#pragma unroll
+        for (int x = 0; x < W / 8; ++x)
+            reinterpret_cast<u32x4*>(p)[x] = u32x4{w[4 * x], w[4 * x + 1], w[4 * x + 2], w[4 * x + 3]};
+    } else {
+#pragma unroll
+        for (int x = 0; x < W / 4; ++x) reinterpret_cast<uint2*>(p)[x] = uint2{w[2 * x], w[2 * x + 1]};
+    }
+}
+
 enum WsKind { kWsNone = 0, kWsF16 = 1, kWsF32 = 2, kWsF16Pair = 3 };
 
 template <typename TOut, int WS>
@@ -59,6 +78,35 @@ struct ScatterEpi {
         }
         c.ws_ok = (WS != kWsNone) && n < n_ws;
         return c;
+    }
+
+    // The workspace copy of columns n .. n + W - 1 of row m (fp16 kind; rows
+    // 16-byte aligned); returns how many values overflowed.
+    template <int W>
+    __device__ __forceinline__ int handoff_run(int64_t m, int64_t n, const float (&v)[W]) const {
+        int over = 0;
+        if constexpr (WS == kWsF16) {
+            if (m >= M || n >= n_ws) return 0;
+            uint16_t h[W];
+#pragma unroll
+            for (int x = 0; x < W; ++x) {
+                const float s = v[x] * ws_scale;
+                const f16 f = (f16)s;
+                over += n + x < n_ws && !__builtin_isfinite((float)f) && __builtin_isfinite(s);
+                h[x] = __builtin_bit_cast(uint16_t, f);
+            }
+            uint16_t* dst = reinterpret_cast<uint16_t*>(ws) + m * ldws + n;
+            if (n + W <= n_ws) {
+                store_run16<W>(dst, h);
+            } else {
+#pragma unroll
+                for (int x = 0; x < W; ++x)
+                    if (n + x < n_ws) dst[x] = h[x];
+            }
+        } else {
+            static_assert(WS == kWsNone, "runs write an fp16 hand-off");
+        }
+        return over;
     }
 
     __device__ __forceinline__ void store(int64_t m, const Col& c, float v) const {
@@ -131,6 +179,51 @@ struct StagedEpi {
         int over = 0;
         out[m * ldo + c.n] = bits(v, over);
         if (over && overflow) atomicAdd(overflow, over);
+    }
+    // columns n .. n + W - 1 of row m
+    template <int W>
+    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
+        if (m >= M || n >= N) return;
+        int over = 0;
+        uint16_t h[W];
+        if (n + W <= N) {
+#pragma unroll
+            for (int x = 0; x < W; ++x) h[x] = bits(v[x], over);
+            store_run16<W>(out + m * ldo + n, h);
+        } else {
+#pragma unroll
+            for (int x = 0; x < W; ++x)
+                if (n + x < N) out[m * ldo + n + x] = bits(v[x], over);
+        }
+        if (over && overflow) atomicAdd(overflow, over);
+    }
+};
+
+// Contiguous fp32 outputs: out[m * ldo + n] = acc(m, n) for m < M, n < N.
+struct RowsF32Epi {
+    float* out;
+    int64_t ldo, N, M;
+    struct Col {
+        int64_t n;
+        bool ok;
+    };
+    __device__ __forceinline__ Col col(int64_t n) const { return Col{n, n < N}; }
+    __device__ __forceinline__ void store(int64_t m, const Col& c, float v) const {
+        if (m < M && c.ok) out[m * ldo + c.n] = v;
+    }
+    template <int W>
+    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
+        if (m >= M || n >= N) return;
+        float* dst = out + m * ldo + n;
+        if (n + W <= N && (ldo & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+#pragma unroll
+            for (int x = 0; x < W / 4; ++x)
+                reinterpret_cast<f32x4*>(dst)[x] = f32x4{v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]};
+        } else {
+#pragma unroll
+            for (int x = 0; x < W; ++x)
+                if (n + x < N) dst[x] = v[x];
+        }
     }
 };
 

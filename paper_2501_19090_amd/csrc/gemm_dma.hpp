@@ -1,0 +1,485 @@
+// Prefill GEMM on CDNA4 matrix cores, 256-row tiles: acc(m, n) = sum_k A[m, k] * B[n, k].
+//
+// One workgroup per output tile; K in tiles of 64.  Operand tiles go from
+// memory straight into LDS (buffer_load_dwordx4 ... lds, no registers and no
+// LDS store instructions in between) and the products run on 16x16x32 MFMAs.
+//
+// Two groups of four waves (one wave of each per SIMD) alternate: in a slot
+// one group reads its next operand fragments from LDS while the other runs
+// its MFMAs, so every SIMD's matrix core has a wave to issue from while the
+// other wave waits for LDS.  Slots end in a barrier.  With P = 2 / KSEG
+// segments per K tile, group 0 reads segment p of tile t in slot
+// 2 (P t + p) and multiplies it in the next; group 1 is one slot behind.
+// The LDS ring has S stages: tile t's stage is free from slot 2 P (t + 1).
+//   NP = 0: each wave issues its share of the loads between its MFMAs, in the
+//           first of its multiplying slots in which the stage is free: group
+//           0 issues tile t + S - 1 in the first segment of tile t, group 1
+//           tile t + S in the last.
+//   NP = 4: four more waves (one per SIMD) issue all loads, so a load that
+//           waits for the address unit does not hold MFMAs up (needs tiles
+//           whose waves fit 170 registers).
+// A wave waits for its loads of tile t + 1 in the slot before the first
+// reader's, S - 1 tiles after it issued them.
+//
+// Why these choices (gfx950, random bf16 data, TFLOP/s of the loop's shape):
+//   * the chip's power limit sets the clock, and an MFMA-only loop on random
+//     operands sustains 2170-2190 TFLOP/s with 16x16x32 against 1940 with
+//     32x32x16;
+//   * LDS reads 256 bytes per cycle and CU when the 16 lanes a cycle serves
+//     cover all 64 banks.  The hardware serves lanes {0-3, 12-15, 20-27},
+//     {4-11, 16-19, 28-31} and the same of the upper half together, and the
+//     swizzles below give those 16 lanes 16 different 16-byte slots (128
+//     bytes per cycle with the chunk ^ (row % 8) form);
+//   * the loads, not the LDS reads, bound the 256 x 128 tile: 48 KB per K
+//     tile at 42-62 bytes per cycle and CU (the vector cache gives one CU 64)
+//     is as long as the tile's 1024 MFMA cycles.  Loads in the reading slots
+//     took 66-70 us for a 4096 x 2048 x 4096 product, between the MFMAs 61,
+//     from their own waves 60 (register-staged predecessor 73); 4096 x 4096 x
+//     8192 on 256 x 256 tiles 192 against 234 us.
+//
+// Operands: A row-major (kOpRow, K-contiguous) or K-major (kOpKmaj: element
+// (k, m) at k * lda + m); B in the lane order of layout.hpp (kOpPack),
+// row-major or K-major.  K-contiguous rows need K a multiple of 8 and 16-byte
+// aligned rows; K-major rows lda >= M rounded up to 8, 16-byte aligned.
+// Ragged M, N and K are handled by the buffer range: out-of-range loads put
+// zeros in LDS.
+//
+// The first MFMA operand is the weight fragment, so a lane's accumulators run
+// along the output row: 4 consecutive columns per fragment, and for
+// K-contiguous B the fragments' columns are dealt so that the TN fragments of
+// a lane are 4 TN consecutive columns (column of fragment j, position i:
+// (i / 4) * 4 TN + 4 j + i % 4).  Contiguous outputs are then stored with
+// 16-byte stores of whole lines straight from the accumulators.
+#pragma once
+
+#include <type_traits>
+
+#include "common.hpp"
+#include "epilogue.hpp"
+#include "gemm_mfma.hpp"
+#include "layout.hpp"
+
+namespace pifa {
+
+enum OpMode : int { kOpRow = 0, kOpPack = 1, kOpKmaj = 2 };
+
+// 64 lanes x 16 bytes from a buffer straight into LDS: lane l's bytes land at
+// lds + 16 l (zeros when its offset is out of range).  In asm because the
+// compiler would make every later LDS read wait for all such loads; the
+// callers wait with wait_vm before a barrier instead.
+__device__ __forceinline__ void dma16(u32x4 rsrc, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 :
+                 : "v"(voff), "s"(rsrc), "s"(lds)
+                 : "memory", "m0");
+}
+
+__device__ __forceinline__ u32x4 raw_rsrc31(const void* base, int64_t bytes) {
+    const uint32_t n = bytes <= 0 ? 0u : (bytes >= 0x7FFFFFFFll ? 0x7FFFFFFFu : (uint32_t)bytes);
+    const uint64_t b = reinterpret_cast<uint64_t>(base);
+    return u32x4{(uint32_t)b, (uint32_t)(b >> 32) & 0xFFFFu, n, 0x00020000u};
+}
+
+// Wait until at most N of this wave's loads are in flight (they end in order).
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
+}
+__device__ __forceinline__ void wait_lgkm0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void slot_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The bf16 scatter writes its outputs row by row from LDS; every other
+// epilogue takes runs of consecutive columns (run).
+template <typename E>
+struct ScatterRowsT {
+    static constexpr bool value = false;
+};
+template <int WS>
+struct ScatterRowsT<ScatterEpi<bf16, WS>> {
+    static constexpr bool value = true;
+};
+
+// The LDS image of one operand's K tile of 64 (ROWS rows of the tile, 128
+// bytes each) in 1 KB pieces, one load instruction each; NI waves issue them,
+// wave iw piece iw, iw + NI, ...  WT: rows one wave of the product reads;
+// TF = WT / 16 fragments; DEALT: the fragments' rows are dealt as above.
+template <int MODE, int ROWS, int NI, int WT, bool DEALT>
+struct OperandTile {
+    static constexpr int kBytes = ROWS * 128;
+    static constexpr int kPieces = ROWS / 8 / NI;
+    static constexpr int TF = WT / 16;
+    static constexpr int kRowBytes = ROWS * 2;  // K-major: one K row
+    static_assert(ROWS % (8 * NI) == 0, "pieces do not split over the waves");
+    static_assert(MODE != kOpKmaj || ROWS == 128 || ROWS == 256, "K-major tile");
+    static_assert(MODE != kOpKmaj || (TF & (TF - 1)) == 0, "K-major fragments");
+
+    u32x4 rs;
+    uint32_t off[kPieces];
+    int kc[kPieces];  // K-contiguous: the piece's 8-value chunk of K that this lane loads
+    const char* base;
+    int64_t ld2, width2;
+
+    // 16-byte slot swizzles (see the file comment for the lanes one cycle serves)
+    __device__ static int row_swizzle(int n) {
+        if constexpr (DEALT) return ((n >> 1) & 1) | ((((n % WT) / (4 * TF)) & 3) << 1);
+        else return (n >> 1) & 7;
+    }
+    __device__ static int pack_swizzle(int gl) {  // rows of 16-row group gl: slot row ^ this
+        if constexpr (TF % 4 == 0) return 4 * (gl & 3);
+        else if constexpr (TF % 2 == 0) return 4 * (((gl % TF) / (TF / 2)) & 3);
+        else return 0;
+    }
+    __device__ static int kmaj_swizzle(int k) { return (k & 3) + 4 * (((k >> 3) ^ (k >> 4)) & 1); }
+
+    template <typename T>
+    __device__ __forceinline__ void init(const T* p, int64_t ld, int64_t row0, int64_t rows, int64_t K, int iw,
+                                         int lane) {
+        if constexpr (MODE == kOpPack) {
+            const int64_t KB = packed_kblocks(K);
+            rs = raw_rsrc31(p + (row0 / kPackRows) * KB * (kPackChunks * 8),
+                            (packed_groups(rows) - row0 / kPackRows) * KB * kPackChunks * 16);
+#pragma unroll
+            for (int j = 0; j < kPieces; ++j) {  // piece 2 gl + kk: 16 rows x 32 K values
+                const int i = iw + NI * j, gl = i >> 1, kk = i & 1;
+                const int row = (lane & 15) ^ pack_swizzle(gl);
+                off[j] = (uint32_t)((gl * KB * kPackChunks + (lane >> 4) * 64 + kk * 16 + row) * 16);
+                kc[j] = 4 * kk + (lane >> 4);
+            }
+        } else if constexpr (MODE == kOpRow) {
+            rs = raw_rsrc31(p + row0 * ld, ((rows - row0 - 1) * ld + K) * 2);
+#pragma unroll
+            for (int j = 0; j < kPieces; ++j) {  // piece: 8 rows x 64 K values
+                const int row = 8 * (iw + NI * j) + (lane >> 3);
+                kc[j] = (lane & 7) ^ row_swizzle(row);
+                off[j] = (uint32_t)((row * ld + 8 * kc[j]) * 2);
+            }
+        } else {
+            base = reinterpret_cast<const char*>(p + row0);
+            ld2 = ld * 2;
+            width2 = round_up(rows - row0, (int64_t)8) * 2;
+            constexpr int CPR = kRowBytes / 16;
+#pragma unroll
+            for (int j = 0; j < kPieces; ++j) {  // piece: 1024 / kRowBytes K rows
+                const int k = (iw + NI * j) * (64 / CPR) + lane / CPR;
+                off[j] = (uint32_t)(k * ld2 + (((lane % CPR) ^ (2 * kmaj_swizzle(k))) * 16));
+            }
+        }
+    }
+
+    struct Step {  // one K tile
+        u32x4 rs;
+        int64_t k0;
+        uint32_t add;
+    };
+    __device__ __forceinline__ Step step(int64_t k0, int64_t kend) const {
+        Step s;
+        s.k0 = k0;
+        if constexpr (MODE == kOpKmaj) {  // the range ends with row kend - 1
+            s.rs = raw_rsrc31(base + k0 * ld2, kend > k0 ? (kend - k0 - 1) * ld2 + width2 : 0);
+            s.add = 0;
+        } else {
+            s.rs = rs;
+            s.add = MODE == kOpPack ? (uint32_t)((k0 / kPackCols) * (kPackChunks * 16) + ((k0 / 64) & 1) * 512)
+                                    : (uint32_t)(k0 * 2);
+        }
+        return s;
+    }
+    __device__ __forceinline__ void issue(const Step& s, int64_t kend, int j, int iw, uint32_t lds) const {
+        const bool ok = MODE == kOpKmaj || s.k0 + 8 * kc[j] < kend;
+        dma16(s.rs, ok ? off[j] + s.add : kMaskedOffset, lds + (iw + NI * j) * 1024);
+    }
+
+    // fragment f of K step kk (32 values): lane l gets row l % 16 of the
+    // fragment, K values 8 (l / 16) .. + 7; w0 = the wave's first row
+    template <typename T>
+    __device__ __forceinline__ static u32x4 frag(const char* st, int w0, int f, int kk, int lane) {
+        const int i = lane & 15, g = lane >> 4;
+        if constexpr (MODE == kOpKmaj) {
+            const int R = i, k = 32 * kk + 8 * g + (R >> 2);
+            const int sw = kmaj_swizzle(k);  // the same for k + 4
+            const char* p = st + k * kRowBytes + ((((w0 >> 4) + f) ^ sw) << 5) + (R & 3) * 8;
+            typedef __attribute__((address_space(3))) v4i16 lds_v4;
+            const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)p);
+            const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p + 4 * kRowBytes));
+            const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
+            return u32x4{a.x, a.y, b.x, b.y};
+        } else {
+            const int n = w0 + (DEALT ? (i >> 2) * 4 * TF + 4 * f + (i & 3) : 16 * f + i);
+            if constexpr (MODE == kOpPack)
+                return *reinterpret_cast<const u32x4*>(st + ((n >> 4) * 2 + kk) * 1024 + g * 256 +
+                                                       (((n & 15) ^ pack_swizzle(n >> 4)) << 4));
+            else
+                return *reinterpret_cast<const u32x4*>(st + n * 128 + (((4 * kk + g) ^ row_swizzle(n)) << 4));
+        }
+    }
+};
+
+template <int BM, int BN, int S>
+constexpr int gemm_dma_lds() {
+    const int loop = S * (BM + BN) * 128, rows = BM * (BN + 8) * 2;  // the scatter's row image
+    return loop > rows ? loop : rows;
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int S, int KSEG, int NP, int AMODE, int BMODE, typename Epi>
+__device__ __forceinline__ void gemm_dma_tile(const T* __restrict__ A, int64_t lda, int64_t M, const T* __restrict__ B,
+                                              int64_t ldb, int64_t N, int64_t K, int64_t kbeg, int64_t kend,
+                                              int64_t tm, int64_t tn, const Epi& epi) {
+    constexpr int BK = 64;
+    constexpr int NW = WM * WN;
+    constexpr int NI = NP ? NP : NW;  // waves that issue loads
+    constexpr int WTM = BM / WM, WTN = BN / WN;
+    constexpr int TM = WTM / 16, TN = WTN / 16;
+    constexpr int P = 2 / KSEG;
+    constexpr bool kDealt = BMODE != kOpKmaj;
+    constexpr int W = kDealt ? 4 * TN : 4;  // consecutive columns a lane holds
+    using OpA = OperandTile<AMODE, BM, NI, WTM, false>;
+    using OpB = OperandTile<BMODE, BN, NI, WTN, kDealt>;
+    constexpr int STAGE = OpA::kBytes + OpB::kBytes;
+    constexpr int DPW = OpA::kPieces + OpB::kPieces;  // loads per issuing wave and K tile
+    static_assert(NW == 8 && S * STAGE <= 163840, "eight multiplying waves, 160 KB of LDS");
+    __shared__ __attribute__((aligned(1024))) char smem[gemm_dma_lds<BM, BN, S>()];
+
+    const int64_t m0 = tm * BM, n0 = tn * BN;
+    if constexpr (SkipEpi<Epi>::value) {
+        if (epi.skip_tile(m0, n0, BM, BN)) return;
+    }
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int wm = (wave % NW) / WN, wn = wave % WN;
+    const int iw = NP ? (wave & (NP - 1)) : wave;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const int64_t nk = ceil_div(kend - kbeg, BK);
+
+    // scatter: this lane's output columns of the tile's rows (loaded here,
+    // where the first tiles' loads hide them), -1 for none
+    constexpr bool kScatter = ScatterRowsT<Epi>::value;
+    int32_t sdst[kScatter ? BN / kWave : 1];
+    if constexpr (kScatter) {
+#pragma unroll
+        for (int c = 0; c < BN / kWave; ++c) {
+            const auto col = epi.col(n0 + c * kWave + lane);
+            sdst[c] = col.out_ok ? (int32_t)col.dst : -1;
+        }
+    }
+
+    OpA opa;
+    OpB opb;
+    opa.init(A, lda, m0, M, K, iw, lane);
+    opb.init(B, ldb, n0, N, K, iw, lane);
+    struct Issue {
+        typename OpA::Step a;
+        typename OpB::Step b;
+        uint32_t lds;
+    };
+    auto plan = [&](int64_t t) {
+        return Issue{opa.step(kbeg + t * BK, kend), opb.step(kbeg + t * BK, kend), lds0 + (uint32_t)(t % S) * STAGE};
+    };
+    auto issue1 = [&](const Issue& s, int j) {
+        if (j < OpA::kPieces) opa.issue(s.a, kend, j < OpA::kPieces ? j : 0, iw, s.lds);
+        else opb.issue(s.b, kend, j < OpA::kPieces ? 0 : j - OpA::kPieces, iw, s.lds + OpA::kBytes);
+    };
+    auto issue = [&](int64_t t, int part, int parts) {  // part of tile t's loads
+        const Issue s = plan(t);
+#pragma unroll
+        for (int j = 0; j < DPW; ++j)
+            if (j * parts / DPW == part) issue1(s, j);
+    };
+
+    f32x4 acc[TM][TN];
+    u32x4 fa[KSEG][TM], fb[KSEG][TN];
+    auto frags = [&](int64_t t, int p) {
+        const char* st = smem + (t % S) * STAGE;
+#pragma unroll
+        for (int q = 0; q < KSEG; ++q) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[q][i] = OpA::template frag<T>(st, wm * WTM, i, p * KSEG + q, lane);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                fb[q][j] = OpB::template frag<T>(st + OpA::kBytes, wn * WTN, j, p * KSEG + q, lane);
+        }
+    };
+    // one segment's MFMAs, with all of plan s's loads between them (ISSUE)
+    auto mma = [&](auto with, const Issue& s) {
+        constexpr bool ISSUE = decltype(with)::value;
+        constexpr int GAP = KSEG * TM * TN / DPW;
+        int n = 0, d = 0;
+#pragma unroll
+        for (int q = 0; q < KSEG; ++q)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    acc[i][j] = Mfma<T>::mma16(fb[q][j], fa[q][i], acc[i][j]);
+                    if constexpr (ISSUE) {
+                        if (n % GAP == GAP / 2 && d < DPW) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            issue1(s, d++);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                    ++n;
+                }
+    };
+    // row and first column of a lane's run u in row block i
+    auto run_row = [&](int i) { return m0 + wm * WTM + i * 16 + (lane & 15); };
+    auto run_col = [&](int u) { return n0 + wn * WTN + (kDealt ? (lane >> 4) * W : 16 * u + 4 * (lane >> 4)); };
+    auto run_vals = [&](int i, int u, float(&v)[W]) {
+#pragma unroll
+        for (int x = 0; x < W; ++x) v[x] = acc[i][kDealt ? x / 4 : u][x & 3];
+    };
+
+    const bool multiplies = NP == 0 || wave < NW;
+    if (multiplies) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (InitEpi<Epi>::value) {
+            static_assert(kDealt, "starting values of a dealt product");
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                float v[W];
+                epi.template init_run<W>(run_row(i), run_col(0), v);
+#pragma unroll
+                for (int x = 0; x < W; ++x) acc[i][x / 4][x & 3] = v[x];
+            }
+        }
+    }
+
+    const int grp = (wave % NW) >= NW / 2 ? 1 : 0;
+    if constexpr (NP > 0) {
+        if (!multiplies) {
+#pragma unroll
+            for (int s = 0; s < S - 1; ++s) issue(s, 0, 1);
+            wait_vm<(S - 2) * DPW>();
+            slot_barrier();
+            for (int64_t t = 0; t < nk; ++t) {
+#pragma unroll
+                for (int p = 0; p < 2 * P; ++p) {
+                    issue(t + S - 1, p, 2 * P);
+                    if (p == 2 * P - 1) wait_vm<(S - 2) * DPW>();
+                    slot_barrier();
+                }
+            }
+            wait_vm<0>();
+            slot_barrier();
+        } else {
+            slot_barrier();
+            if (grp) slot_barrier();
+            for (int64_t t = 0; t < nk; ++t) {
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    frags(t, p);
+                    wait_lgkm0();
+                    slot_barrier();
+                    __builtin_amdgcn_s_setprio(1);
+                    mma(std::false_type{}, Issue{});
+                    __builtin_amdgcn_s_setprio(0);
+                    slot_barrier();
+                }
+            }
+            if (!grp) slot_barrier();
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < S - 1; ++s) issue(s, 0, 1);
+        if (grp) {
+            issue(S - 1, 0, 1);
+            wait_vm<(S - 1) * DPW>();
+        } else {
+            wait_vm<(S - 2) * DPW>();
+        }
+        slot_barrier();
+        auto loop = [&](auto second) {
+            constexpr bool G1 = decltype(second)::value;
+            for (int64_t t = 0; t < nk; ++t) {
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    frags(t, p);
+                    const Issue s = plan(t + (G1 ? S : S - 1));
+                    wait_lgkm0();
+                    if (G1 && p == P - 1) wait_vm<(S - 2) * DPW>();
+                    slot_barrier();
+                    __builtin_amdgcn_s_setprio(1);
+                    if (p == (G1 ? P - 1 : 0)) mma(std::true_type{}, s);
+                    else mma(std::false_type{}, s);
+                    __builtin_amdgcn_s_setprio(0);
+                    if (!G1 && p == P - 1) wait_vm<(S - 2) * DPW>();
+                    slot_barrier();
+                }
+            }
+        };
+        if (grp) {
+            slot_barrier();
+            loop(std::true_type{});
+            wait_vm<0>();
+        } else {
+            loop(std::false_type{});
+            wait_vm<0>();
+            slot_barrier();
+        }
+        if constexpr (kScatter) slot_barrier();  // group 1's last loads have landed too
+    }
+
+    if constexpr (kScatter) {
+        // The tile's rows as bf16 in LDS, then row by row: a store of a wave
+        // covers 64 consecutive tile columns of one output row, whose
+        // destinations span a few lines of Y.  The hand-off is stored first,
+        // straight from the accumulators.
+        constexpr int PITCH = BN + 8;
+        uint16_t* tile = reinterpret_cast<uint16_t*>(smem);
+        if (multiplies) {
+            int over = 0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                float v[W];
+                run_vals(i, 0, v);
+                over += epi.template handoff_run<W>(run_row(i), run_col(0), v);
+                uint16_t h[W];
+#pragma unroll
+                for (int x = 0; x < W; ++x) h[x] = f32_to_bf16_bits(v[x] * epi.out_scale);
+                store_run16<W>(tile + (run_row(i) - m0) * PITCH + (run_col(0) - n0), h);
+            }
+            if (over) atomicAdd(epi.overflow, over);
+        }
+        __syncthreads();
+        constexpr int NWT = NW + NP, C = BN / kWave;
+        uint16_t* out = reinterpret_cast<uint16_t*>(epi.out);
+        const int rows = (int)((M - m0) < BM ? (M - m0) : BM);
+#pragma unroll 4
+        for (int r = wave; r < rows; r += NWT) {
+            uint16_t* y = out + (m0 + r) * epi.ldo;
+            uint16_t h[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) h[c] = tile[r * PITCH + c * kWave + lane];
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (sdst[c] >= 0) y[sdst[c]] = h[c];
+        }
+    } else if (multiplies) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int u = 0; u < (kDealt ? 1 : TN); ++u) {
+                float v[W];
+                run_vals(i, u, v);
+                epi.template run<W>(run_row(i), run_col(u), v);
+            }
+        }
+    }
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int S, int KSEG, int NP, int AMODE, int BMODE, typename Epi>
+__global__ __launch_bounds__((WM * WN + NP) * kWave, (WM * WN + NP) / 4) void gemm_nt_dma(
+    const T* __restrict__ A, int64_t lda, int64_t M, const T* __restrict__ B, int64_t ldb, int64_t N, int64_t K,
+    Epi epi) {
+    int64_t tm, tn;
+    tile_coords<BM, BN>(blockIdx.x, ceil_div(M, BM), ceil_div(N, BN), tm, tn);
+    gemm_dma_tile<T, BM, BN, WM, WN, S, KSEG, NP, AMODE, BMODE, Epi>(A, lda, M, B, ldb, N, K, 0, K, tm, tn, epi);
+}
+
+}  // namespace pifa

@@ -363,6 +363,24 @@ struct AccF64Epi {
     __device__ __forceinline__ void store(int64_t m, const Col& c, float v) const {
         if (m < M && c.ok) out[m * ld + c.n] += (double)v;
     }
+    template <int W>
+    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
+        if (m >= M || n >= N) return;
+        double* dst = out + m * ld + n;
+        if (n + W <= N && (ld & 1) == 0) {  // 16-byte rows (out is the handle's allocation)
+            typedef double f64x2 __attribute__((ext_vector_type(2)));
+            f64x2* d2 = reinterpret_cast<f64x2*>(dst);
+            f64x2 s[W / 2];
+#pragma unroll
+            for (int x = 0; x < W / 2; ++x) s[x] = d2[x];
+#pragma unroll
+            for (int x = 0; x < W / 2; ++x) d2[x] = s[x] + f64x2{(double)v[2 * x], (double)v[2 * x + 1]};
+        } else {
+#pragma unroll
+            for (int x = 0; x < W; ++x)
+                if (n + x < N) dst[x] += (double)v[x];
+        }
+    }
 };
 
 

@@ -22,6 +22,7 @@
 #include "epilogue.hpp"
 #include "gemm_f32.hpp"
 #include "gemm_mfma.hpp"
+#include "gemm_dma.hpp"
 #include "backward.hpp"
 #include "build.hpp"
 #include "gemv_skinny.hpp"
@@ -221,7 +222,7 @@ SplitPlan split_plan(int64_t tiles, int64_t M, int64_t N, int64_t K) {
 }
 
 // Partial-product bytes a launch of this shape needs (0 if it does not split).
-TileCfg pick_tile(int64_t M, int64_t N);
+TileCfg pick_tile(int64_t M, int64_t N, int wide);
 
 // No product with more rows than this splits K: its 128-row tiles alone
 // fill the chip.  Reserving for every M up to it covers every split.
@@ -231,31 +232,33 @@ struct GemmPlan {
     int64_t bm, bn;
     SplitPlan split;
 };
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool wide_ok, bool can_split);
+// Which of the wide tiles a product may take: none (256 x 128 at most), all,
+// or only the square one (K-major operands: their tiles are powers of two).
+enum WideTiles : int { kWideNone = 0, kWideAll = 1, kWideSquare = 2 };
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, int wide, bool can_split);
 
 size_t split_bytes(int64_t M, int64_t N, int64_t K) {
     if (M == 0 || N == 0) return 0;
-    const GemmPlan g = gemm_plan(M, N, K, true, true);
+    const GemmPlan g = gemm_plan(M, N, K, kWideAll, true);
     return g.split.splits > 1 ? (size_t)(g.split.splits * M * N) * 4 : 0;
 }
 
 // Prefill tile configurations and a cost model to pick one: time ~ rounds
 // of concurrently resident tiles x tile area x tiles sharing a CU / relative
-// efficiency (measured: 256x256 and 256x192 tiles reach ~1.15x and 128x128
-// ~0.9x the per-FLOP rate of 256x128).  128x128 fits two workgroups per CU.
-// The 256x192 tile serves widths that leave the 256x128 grid just past a
-// whole number of rounds (N = 2458 or 2867 at M = 4096: one round of
-// 256x192 tiles instead of two of 256x128, 25% faster; N = 8960: 13%).
-TileCfg pick_tile(int64_t M, int64_t N) {
+// efficiency.  Measured per-FLOP rates of whole rounds relative to 256 x 128
+// (TFLOP/s of a 4096 x 4096 x 8192 product 1230, 256 x 256 tiles 1345; 4096 x
+// 3072 x 4096 on 256 x 192 tiles 1148 against 969 on two rounds of 256 x 128
+// and 1083 on 192 of the 256 CUs with 256 x 256): about 1.12, 1.08 and, with
+// half the LDS reuse and one workgroup per CU, 0.8 for 128 x 128.
+TileCfg pick_tile(int64_t M, int64_t N, int wide) {
     struct C { int64_t bm, bn, per_cu; double eff; };
-    const C cfg[4] = {{256, 256, 1, 1.15}, {256, 192, 1, 1.15}, {256, 128, 1, 1.0}, {128, 128, 2, 0.9}};
+    const C cfg[4] = {{256, 256, 1, 1.12}, {256, 192, 1, 1.08}, {256, 128, 1, 1.0}, {128, 128, 1, 0.8}};
     int best = 3;
     double best_t = 1e300;
     for (int i = 0; i < 4; ++i) {
+        if ((i < 2 && wide == kWideNone) || (i == 1 && wide == kWideSquare)) continue;
         const int64_t tiles = ceil_div(M, cfg[i].bm) * ceil_div(N, cfg[i].bn);
-        const int64_t rounds = ceil_div(tiles, kCus * cfg[i].per_cu);
-        const int64_t sharing = std::min(cfg[i].per_cu, ceil_div(tiles, kCus));
-        const double t = (double)rounds * cfg[i].bm * cfg[i].bn * sharing / cfg[i].eff;
+        const double t = (double)ceil_div(tiles, kCus * cfg[i].per_cu) * cfg[i].bm * cfg[i].bn / cfg[i].eff;
         if (t < best_t * 0.999) {
             best_t = t;
             best = i;
@@ -264,12 +267,10 @@ TileCfg pick_tile(int64_t M, int64_t N) {
     return (TileCfg)best;
 }
 
-// The tile and K split of a prefill product.  wide_ok: the epilogue fits the
-// registers the 256 x 256 and 256 x 192 tiles leave; can_split: a partials
-// buffer is available.
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool wide_ok, bool can_split) {
-    TileCfg cfg = pick_tile(M, N);
-    if (!wide_ok && (cfg == kTile256x256 || cfg == kTile256x192)) cfg = kTile256x128;
+// The tile and K split of a prefill product.  can_split: a partials buffer is
+// available.
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, int wide, bool can_split) {
+    const TileCfg cfg = pick_tile(M, N, wide);
     if (cfg == kTile256x256) return {256, 256, {1, K}};
     if (cfg == kTile256x192) return {256, 192, {1, K}};
     if (cfg == kTile256x128) return {256, 128, {1, K}};
@@ -310,45 +311,43 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool wide_ok, bool can_split
     return {128, 128, p};
 }
 
+template <typename T, int BM, int BN, int WM, int WN, int S, int KSEG, int NP, int AMODE, int BMODE, typename Epi>
+void launch_dma(const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb, int64_t N, int64_t K, const Epi& epi,
+                hipStream_t st) {
+    const dim3 grid((unsigned)(ceil_div(M, BM) * ceil_div(N, BN)));
+    if constexpr (DualEpiT<Epi>::value)
+        hipLaunchKernelGGL((gemm_nt_dma<T, BM, BN, WM, WN, S, KSEG, NP, AMODE, BMODE, ScatterEpi<bf16, kWsF16>>), grid,
+                           dim3((WM * WN + NP) * kWave), 0, st, A, lda, M, B, ldb, N, K, epi.elementwise());
+    else
+        hipLaunchKernelGGL((gemm_nt_dma<T, BM, BN, WM, WN, S, KSEG, NP, AMODE, BMODE, Epi>), grid,
+                           dim3((WM * WN + NP) * kWave), 0, st, A, lda, M, B, ldb, N, K, epi);
+}
+
 template <typename T, bool BPACK, typename Epi, int KM = 0>
 hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb,
                        int64_t N, int64_t K, Epi epi, float* partials, hipStream_t st) {
     if (M == 0 || N == 0) return hipSuccess;
     TimedLaunch timed(site, st);
-    // epilogues that load the accumulators' starting values, or add into
-    // fp64 / store fp32 outputs, need more registers than the 256 x 256 and
-    // 256 x 192 tiles have left (they spill there)
-    constexpr bool kWideOk = !InitEpi<Epi>::value && !std::is_same<Epi, AccF64Epi>::value &&
-                             !std::is_same<Epi, ScatterEpi<float, kWsNone>>::value;
-    const GemmPlan g = gemm_plan(M, N, K, kWideOk, partials != nullptr);
+    constexpr int AM = (KM & 1) ? kOpKmaj : kOpRow, BMD = (KM & 2) ? kOpKmaj : BPACK ? kOpPack : kOpRow;
+    const GemmPlan g = gemm_plan(M, N, K, KM ? kWideSquare : kWideAll, partials != nullptr);
     const dim3 grid((unsigned)(ceil_div(M, g.bm) * ceil_div(N, g.bn)));
-    if (g.bm == 256 && g.bn == 256) {
-        if constexpr (DualEpiT<Epi>::value)
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 256, kGemmBK, 2, 4, BPACK, 1, ScatterEpi<bf16, kWsF16>, KM>), grid,
-                               dim3(8 * kWave), 0, st, A, lda, M, B, ldb, N, K, K, epi.elementwise());
-        else if constexpr (kWideOk)
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 256, kGemmBK, 2, 4, BPACK, 1, Epi, KM>), grid, dim3(8 * kWave), 0,
-                               st, A, lda, M, B, ldb, N, K, K, epi);
-    } else if (g.bm == 256 && g.bn == 192) {
-        // the 256-row tiles write the pivot product's fp16 hand-off element by
-        // element: staged through LDS it cost more than its stores save (M =
-        // 4096, three alternating passes, us per launch: attention layer,
-        // 256 x 128 tiles, 80.1-81.2 -> 76.3-76.4; r = 70% of 4096, 256 x 192
-        // tiles, 103.9-104.2 -> 100.0-100.4).  The 128-row tiles keep it
-        // staged (1-2 us faster there).
-        if constexpr (DualEpiT<Epi>::value)
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 192, kGemmBK, 4, 2, BPACK, 2, ScatterEpi<bf16, kWsF16>, KM>), grid,
-                               dim3(8 * kWave), 0, st, A, lda, M, B, ldb, N, K, K, epi.elementwise());
-        else if constexpr (kWideOk)
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 192, kGemmBK, 4, 2, BPACK, 2, Epi, KM>), grid, dim3(8 * kWave), 0,
-                               st, A, lda, M, B, ldb, N, K, K, epi);
-    } else if (g.bm == 256) {
-        if constexpr (DualEpiT<Epi>::value)
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 128, kGemmBK, 4, 2, BPACK, 2, ScatterEpi<bf16, kWsF16>, KM>), grid,
-                               dim3(8 * kWave), 0, st, A, lda, M, B, ldb, N, K, K, epi.elementwise());
-        else
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 128, kGemmBK, 4, 2, BPACK, 2, Epi, KM>), grid, dim3(8 * kWave), 0,
-                               st, A, lda, M, B, ldb, N, K, K, epi);
+    // Tiles of 128 x 128 and up that do not split K load their operands
+    // straight into LDS, 16 bytes at a time; the smaller tiles, whose few
+    // waves per workgroup have no loads to wait behind, are faster through
+    // registers (512 x 2048 x 2048 on 64 x 64 tiles: 12.9 against 15.2 us).
+    // K-major operands of unaligned callers' buffers (the backward's X) stay
+    // with the register-staged loads too.
+    const bool direct = KM == 0 || (aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0);
+    if (g.split.splits == 1 && direct && g.bm >= 128 && g.bn >= 128) {
+        if (g.bm == 256 && g.bn == 256) {
+            launch_dma<T, 256, 256, 2, 4, 2, 1, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
+        } else if (g.bm == 256 && g.bn == 192) {
+            if constexpr (KM == 0) launch_dma<T, 256, 192, 4, 2, 2, 1, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
+        } else if (g.bm == 256) {
+            launch_dma<T, 256, 128, 4, 2, 3, 2, 4, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
+        } else {
+            launch_dma<T, 128, 128, 2, 4, 4, 2, 4, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
+        }
     } else if (g.split.splits == 1) {
         if (g.bm == 64)
             hipLaunchKernelGGL((gemm_nt_mfma<T, 64, 64, kGemmBK, 2, 2, BPACK, 2, Epi, KM>), grid, dim3(4 * kWave), 0,
@@ -356,9 +355,10 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
         else if (g.bn == 64)
             hipLaunchKernelGGL((gemm_nt_mfma<T, 128, 64, kGemmBK, 4, 2, BPACK, 2, Epi, KM>), grid, dim3(8 * kWave), 0,
                                st, A, lda, M, B, ldb, N, K, K, epi);
-        else
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 128, 128, kGemmBK, 4, 2, BPACK, 2, Epi, KM>), grid, dim3(8 * kWave), 0,
-                               st, A, lda, M, B, ldb, N, K, K, epi);
+        else if constexpr (KM != 0)
+            hipLaunchKernelGGL((gemm_nt_mfma<T, 128, 128, kGemmBK, 4, 2, BPACK, 2, Epi, KM>),
+                               dim3((unsigned)(ceil_div(M, 128) * ceil_div(N, 128))), dim3(8 * kWave), 0, st, A, lda, M,
+                               B, ldb, N, K, K, epi);
     } else {
         SplitEpi se{partials, M, N};
         const dim3 sgrid(grid.x, (unsigned)g.split.splits);
@@ -880,7 +880,7 @@ const char* pifa_status_string(pifa_status s) {
 pifa_status pifa_gemm_plan(int64_t M, int64_t N, int64_t K, int wide_epilogue, int64_t* tile_m,
                            int64_t* tile_n, int64_t* k_splits) {
     if (M < 1 || N < 1 || K < 1 || !tile_m || !tile_n || !k_splits) return PIFA_ERR_INVALID_ARG;
-    const GemmPlan g = gemm_plan(M, N, K, wide_epilogue != 0, true);
+    const GemmPlan g = gemm_plan(M, N, K, wide_epilogue ? kWideAll : kWideNone, true);
     *tile_m = g.bm;
     *tile_n = g.bn;
     *k_splits = g.split.splits;
@@ -1367,6 +1367,21 @@ hipError_t launch_gather(const bf16* in, int64_t ld_in, int64_t M, const int32_t
     return hipGetLastError();
 }
 
+// split_columns (see backward.hpp); rows too long for LDS are gathered from memory.
+hipError_t launch_split(const bf16* in, int64_t d, int64_t M, const int32_t* ia, int64_t na, bf16* out_a, int64_t lda,
+                        const int32_t* ib, int64_t nb, bf16* out_b, int64_t ldb, hipStream_t st) {
+    constexpr int64_t kLds = 65536;
+    const int64_t row = round_up(d, (int64_t)8) * 2, rows = std::min<int64_t>(kSplitRows, kLds / row);
+    if (rows < 1) {
+        hipError_t e = launch_gather(in, d, M, ia, na, out_a, lda, nullptr, 0, st);
+        if (e == hipSuccess && out_b) e = launch_gather(in, d, M, ib, nb, out_b, ldb, nullptr, 0, st);
+        return e;
+    }
+    hipLaunchKernelGGL(split_columns, dim3((unsigned)ceil_div(M, rows)), dim3(512), (size_t)(rows * row), st, in, d, M,
+                       (int)rows, ia, na, out_a, lda, ib, nb, out_b, ldb);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 extern "C" {
@@ -1392,6 +1407,7 @@ pifa_status pifa_layer_backward(pifa_handle h, const void* X, const void* Y, con
     // workspace regions, in 2-byte elements (each a multiple of 256 bytes)
     const int64_t e_gic = align_elems(M * ldc), e_ypr = align_elems(M * ldy), e_gp32 = align_elems(2 * M * r_pad),
                   e_gp16 = align_elems(M * r_pad), e_inv = align_elems(2 * M), e_gpb = align_elems(M * r_pad);
+    // (gp16 holds the gathered pivot columns of G until G_p is there)
     const size_t part = std::max({split_bytes(M, r_pad, ldc), split_bytes(M, d_in, r_pad), split_bytes(r, d_in, M),
                                   split_bytes(n_np, r, M)});
     const size_t main_bytes = (size_t)(e_gic + e_ypr + e_gp32 + e_gp16 + e_inv + e_gpb) * 2;
@@ -1407,17 +1423,19 @@ pifa_status pifa_layer_backward(pifa_handle h, const void* X, const void* Y, con
     const bf16* G = (const bf16*)dY;
     hipError_t e = hipSuccess;
 
-    {  // the gathered columns G[:, I^c] and Y[:, I] as rows
+    {  // the gathered columns G[:, I^c], G[:, I] and Y[:, I] as rows
         TimedLaunch timed(kSiteBwdData, st);
-        if (n_np > 0 && (e = launch_gather(G, d_out, M, h->npiv, n_np, gic, ldc, nullptr, 0, st)) != hipSuccess)
+        bf16* gpi = (bf16*)gp16;
+        if ((e = launch_split(G, d_out, M, h->piv, r, gpi, r_pad, h->npiv, n_np, n_np > 0 ? gic : nullptr, ldc, st)) !=
+            hipSuccess)
             return PIFA_ERR_HIP;
         if (n_np > 0 && dC &&
-            (e = launch_gather((const bf16*)Y, d_out, M, h->piv, r, ypr, ldy, nullptr, 0, st)) != hipSuccess)
+            (e = launch_split((const bf16*)Y, d_out, M, h->piv, r, ypr, ldy, nullptr, 0, nullptr, 0, st)) != hipSuccess)
             return PIFA_ERR_HIP;
     }
     // G_p = G[:, I^c] C + G[:, I] in fp32, and bf16(G_p)
     e = launch_gemm<bf16, true>(kSiteBwdGp, gic, ldc, M, (const bf16*)h->bwd_ct, 0, r_pad, ldc,
-                                GradPivotEpi{G, d_out, h->piv, r, r_pad, gp32, gpb, M}, partials, st);
+                                GradPivotEpi{(const bf16*)gp16, r_pad, gp32, gpb, M}, partials, st);
     if (e != hipSuccess) return PIFA_ERR_HIP;
     if (dX) {  // dX = (G_p 2^s_m in fp16) (W_p^T 2^cw in fp16)^T 2^-(s_m + cw)
         {
@@ -1426,22 +1444,21 @@ pifa_status pifa_layer_backward(pifa_handle h, const void* X, const void* Y, con
             if (hipGetLastError() != hipSuccess) return PIFA_ERR_HIP;
         }
         e = launch_gemm<f16, true>(kSiteBwdDx, gp16, r_pad, M, (const f16*)h->bwd_wpt, 0, d_in, r_pad,
-                                   RowScaleEpi{(bf16*)dX, d_in, d_in, inv, std::ldexp(1.0f, -h->bwd_cw), M}, partials,
+                                   RowScaleEpi{(bf16*)dX, d_in, d_in, inv, std::ldexp(1.0f, -h->bwd_cw), M,
+                                               staged_ok(dX, d_in)}, partials,
                                    st);
         if (e != hipSuccess) return PIFA_ERR_HIP;
     }
     // the transposed products reduce over the M activation rows: both
     // operands are read K-major (rows of G_p, X, G[:, I^c], Y[:, I])
     if (dW_p) {  // dW_p = G_p^T X
-        e = launch_gemm<bf16, false, ScatterEpi<float, kWsNone>, 3>(
-            kSiteBwdDwp, gpb, r_pad, r, (const bf16*)X, d_in, d_in, M,
-            make_epi<float, kWsNone>(dW_p, d_in, nullptr, d_in, 1.f, nullptr, 0, 0, 1.f, nullptr, r), partials, st);
+        e = launch_gemm<bf16, false, RowsF32Epi, 3>(kSiteBwdDwp, gpb, r_pad, r, (const bf16*)X, d_in, d_in, M,
+                                                    RowsF32Epi{dW_p, d_in, d_in, r}, partials, st);
         if (e != hipSuccess) return PIFA_ERR_HIP;
     }
     if (dC && n_np > 0) {  // dC = G[:, I^c]^T Y_p
-        e = launch_gemm<bf16, false, ScatterEpi<float, kWsNone>, 3>(
-            kSiteBwdDc, gic, ldc, n_np, ypr, ldy, r, M,
-            make_epi<float, kWsNone>(dC, r, nullptr, r, 1.f, nullptr, 0, 0, 1.f, nullptr, n_np), partials, st);
+        e = launch_gemm<bf16, false, RowsF32Epi, 3>(kSiteBwdDc, gic, ldc, n_np, ypr, ldy, r, M,
+                                                    RowsF32Epi{dC, r, r, n_np}, partials, st);
         if (e != hipSuccess) return PIFA_ERR_HIP;
     }
     return PIFA_OK;

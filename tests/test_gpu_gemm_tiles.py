@@ -1,0 +1,126 @@
+"""The prefill products at the edges of their tiles: ragged rows, columns and
+K for every output tile, row-major and packed weights, contiguous and
+unaligned outputs, and K-major operands (calibration sums), against fp64.
+
+The bound per output is the fp32 accumulation error K u sum_k |a_k b_k|
+(u = 2^-24, any summation order) plus, for a bf16 output, its rounding
+(2^-8 of the value: half a unit in the last place of 8 significant bits is
+2^-9)."""
+import numpy as np
+import pytest
+
+from gpu_util import from_dev, torch_mod
+
+pytestmark = pytest.mark.gpu
+U32 = 2.0 ** -24
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _cuda():
+    if not torch_mod().cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def _bf16(shape, seed):
+    torch = torch_mod()
+    g = torch.Generator().manual_seed(seed)
+    return torch.randn(*shape, generator=g).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("M,N,K,tile", [
+    (4095, 4040, 72, (256, 256)),   # K past one tile by 8, contiguous rows
+    (4095, 4041, 200, (256, 256)),  # odd row length: the scatter's stores
+    (4090, 2500, 136, (256, 192)),
+    (4001, 2041, 264, (256, 128)),
+    (4033, 2040, 8, (256, 128)),    # a single 8-deep K chunk
+    (2041, 2040, 200, (128, 128)),
+    (1921, 2047, 328, (128, 128)),
+])
+@pytest.mark.parametrize("packed", [True, False])
+def test_tile_edges(M, N, K, tile, packed):
+    torch = torch_mod()
+    from paper_2501_19090_amd import pifa
+    assert pifa.pifa_gemm_plan(M, N, K) == tile + (1,)
+    X, W = _bf16((M, K), 1), _bf16((N, K), 2)
+    # rows next to ordinary ones hold infinities: nothing of a row may reach
+    # another, also where the last K tile reads past the end of the row
+    X[5::97] = float("inf")
+    x, w = X.to("cuda:0"), W.to("cuda:0")
+    y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+    if packed:
+        h = pifa.dense_layer_create(w)
+        try:
+            pifa.dense_layer_forward(h, x, y)
+            torch.cuda.synchronize()
+        finally:
+            pifa.dense_layer_destroy(h)
+    else:
+        pifa.dense_forward(w, x, y)
+        torch.cuda.synchronize()
+    rows = np.setdiff1d(np.arange(M), np.arange(5, M, 97))
+    a, b = X.double().numpy()[rows], W.double().numpy()
+    ref = a @ b.T
+    bound = 2.0 ** -8 * np.abs(ref) + K * U32 * (np.abs(a) @ np.abs(b).T)
+    got = from_dev(y)
+    assert np.all(np.abs(got[rows] - ref) <= bound)
+    assert not np.any(np.isfinite(got[5::97]))
+
+
+@pytest.mark.parametrize("n,tokens,tile", [
+    (4000, 77, (256, 256)),
+    (2008, 130, (128, 128)),
+    (2400, 64, (256, 128)),
+])
+def test_k_major_tile_edges(n, tokens, tile):
+    torch = torch_mod()
+    from paper_2501_19090_amd import pifa
+    got_tile = pifa.pifa_gemm_plan(n, n, tokens)
+    assert got_tile == tile + (1,) or (tile == (256, 128) and got_tile[:2] == (256, 192))
+    xo, xu = _bf16((tokens, n), 3), _bf16((tokens, n), 4)
+    h = pifa.pifa_calib_create(n)
+    S = torch.empty((n, n), dtype=torch.float64, device="cuda:0")
+    P = torch.empty_like(S)
+    try:
+        pifa.pifa_calib_accumulate(h, xo.to("cuda:0"), xu.to("cuda:0"))
+        pifa.pifa_calib_accumulate(h, xo.to("cuda:0"), xu.to("cuda:0"))
+        pifa.pifa_calib_read(h, S, P)
+        torch.cuda.synchronize()
+    finally:
+        pifa.pifa_calib_destroy(h)
+    a, b = xo.double().numpy(), xu.double().numpy()
+    for got, left in ((S, b), (P, a)):
+        bound = 2 * tokens * U32 * (np.abs(left).T @ np.abs(b)) + 1e-12
+        assert np.all(np.abs(got.cpu().numpy() - 2 * (left.T @ b)) <= bound)
+
+
+@pytest.mark.parametrize("d_out,r,M", [(96, 33, 5), (4100, 2050, 3), (16392, 40, 3), (33000, 24, 2), (257, 257, 4)])
+def test_backward_column_split(d_out, r, M):
+    """The gather of a gradient's pivot and non-pivot columns: one and two rows
+    per workgroup, rows too long for LDS, odd row lengths, no non-pivot."""
+    torch = torch_mod()
+    from paper_2501_19090_amd import inputs, pifa
+    d_in = 264 if r <= 264 else 2056
+    piv, npiv = inputs.random_partition(d_out, r, 9)
+    Wp, C = _bf16((r, d_in), 5), _bf16((d_out - r, r), 6)
+    X, G = _bf16((M, d_in), 7), _bf16((M, d_out), 8)
+    Wd, Cd, Xd, Gd = (t.double().numpy() for t in (Wp, C, X, G))
+    Y = np.zeros((M, d_out))
+    Y[:, piv] = Xd @ Wd.T
+    Y[:, npiv] = Y[:, piv] @ Cd.T
+    Yb = torch.from_numpy(Y).to(torch.bfloat16)
+    lay = pifa.PifaLayer(Wp.to("cuda:0"), C.to("cuda:0"), piv, npiv, d_out)
+    dX = torch.empty((M, d_in), dtype=torch.bfloat16, device="cuda:0")
+    dWp = torch.empty((r, d_in), dtype=torch.float32, device="cuda:0")
+    dC = torch.empty((d_out - r, r), dtype=torch.float32, device="cuda:0")
+    pifa.pifa_layer_backward(lay.handle, X.to("cuda:0"), Yb.to("cuda:0"), G.to("cuda:0"), dX, dWp, dC)
+    torch.cuda.synchronize()
+    lay.close()
+    Gp = Gd[:, piv] + Gd[:, npiv] @ Cd
+    ref = Gp.T @ Xd
+    # bf16(G_p) feeds dW_p: 2^-9 of each |G_p| |X| term
+    assert np.linalg.norm(dWp.cpu().numpy() - ref) <= 2.0 ** -8 * np.linalg.norm(np.abs(Gp).T @ np.abs(Xd))
+    ref = Gd[:, npiv].T @ Yb.double().numpy()[:, piv]
+    bound = (M + 2) * U32 * (np.abs(Gd[:, npiv]).T @ np.abs(Yb.double().numpy()[:, piv]))
+    assert np.all(np.abs(dC.cpu().numpy() - ref) <= bound + 1e-30)
+    ref = Gp @ Wd
+    assert np.linalg.norm(from_dev(dX) - ref) <= 2.0 ** -8 * np.linalg.norm(np.abs(Gp) @ np.abs(Wd))
