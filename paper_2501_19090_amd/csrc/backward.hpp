@@ -166,15 +166,15 @@ __global__ __launch_bounds__(256) void gather_tile(const bf16* __restrict__ in, 
 
 // Rows of in (M x d, row stride d) split by column sets: out_a[m][j] =
 // in[m][ia[j]] for j < na (zeros up to lda) and, if out_b, out_b[m][j] =
-// in[m][ib[j]] for j < nb (zeros up to ldb); lda and ldb are multiples of 8
-// and the outputs 16-byte aligned.  One workgroup takes R rows: they are read
-// once, whole lines at a time, into LDS, and the outputs gathered
-// from there, 8 columns of one index load and one 16-byte store per row.  The
-// bound is memory: for a 4096 x 4096 gradient split in halves 67 MB in 15 us,
-// where a gather of each half alone, 2 bytes per load, read every line of the
-// rows for it and took 15 us.
+// in[m][ib[j]] for j < nb (zeros up to ldb); lda and ldb are even and the
+// outputs 4-byte aligned.  One workgroup takes R rows: they are read once,
+// whole lines at a time, into LDS, and gathered from there, a lane taking two
+// neighbouring columns of every row: with sorted indices the 2-byte LDS reads
+// of a wave span a few hundred bytes (8 columns per lane, for 16-byte stores,
+// put 8 lanes on each bank: 25 us per 4096 x 4096 matrix where this takes 15), and a wave's
+// stores are 256 contiguous bytes.  Bound: memory.
 // Dynamic LDS: R * round_up(d, 8) * 2 bytes.
-constexpr int kSplitRows = 2;  // R where two rows fit 64 KB
+constexpr int kSplitRows = 4;  // R where they fit 64 KB
 
 __global__ __launch_bounds__(512) void split_columns(const bf16* __restrict__ in, int64_t d, int64_t M, int R,
                                                      const int32_t* __restrict__ ia, int64_t na,
@@ -195,15 +195,11 @@ __global__ __launch_bounds__(512) void split_columns(const bf16* __restrict__ in
     }
     __syncthreads();
     auto gather = [&](const int32_t* __restrict__ idx, int64_t n, bf16* __restrict__ out, int64_t ld) {
-        for (int64_t j = 8 * (int64_t)threadIdx.x; j < ld; j += 8 * 512) {
-            int32_t c[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) c[e] = idx[j + e < n ? j + e : n - 1];
+        for (int64_t j = 2 * (int64_t)threadIdx.x; j < ld; j += 2 * 512) {
+            const int32_t c0 = idx[j < n ? j : n - 1], c1 = idx[j + 1 < n ? j + 1 : n - 1];
             for (int r = 0; r < nr; ++r) {
-                uint16_t v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = j + e < n ? rows[r * pitch + c[e]] : (uint16_t)0;
-                store_run16<8>(reinterpret_cast<uint16_t*>(out) + (m0 + r) * ld + j, v);
+                const uint32_t lo = j < n ? rows[r * pitch + c0] : 0, hi = j + 1 < n ? rows[r * pitch + c1] : 0;
+                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + (m0 + r) * ld + j) = lo | (hi << 16);
             }
         }
     };
