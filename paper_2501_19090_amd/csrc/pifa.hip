@@ -6,7 +6,7 @@
 //   GEMM2  Y_np = Y_p C^T          -> Y[:, nonpivot_idx]
 // Both assignments are fused into the producing kernel's epilogue.  M > 16
 // runs the LDS-tiled MFMA GEMM; M <= 16 runs the weight-streaming skinny
-// MFMA kernel.  fp32 layers use the fp32 vector-ALU kernel.
+// MFMA kernel.  fp32 layers run on the fp32 matrix cores.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -20,9 +20,9 @@
 #include "../../include/pifa.h"
 #include "common.hpp"
 #include "epilogue.hpp"
-#include "gemm_f32.hpp"
 #include "gemm_mfma.hpp"
 #include "gemm_dma.hpp"
+#include "gemm_f32.hpp"
 #include "backward.hpp"
 #include "build.hpp"
 #include "gemv_skinny.hpp"
@@ -383,8 +383,26 @@ hipError_t launch_gemm_f32(int site, const float* A, int64_t lda, int64_t M, con
                            int64_t ldb, int64_t N, int64_t K, Epi epi, hipStream_t st) {
     if (M == 0 || N == 0) return hipSuccess;
     TimedLaunch timed(site, st);
-    hipLaunchKernelGGL((gemm_nt_f32<Epi>), dim3((unsigned)ceil_div(N, 64), (unsigned)ceil_div(M, 64)),
-                       dim3(256), 0, st, A, lda, M, B, ldb, N, K, epi);
+    // 64 x 64 tiles (two workgroups per CU) where they come close to filling the
+    // chip; fewer than that leave CUs idle for the whole of K, and 32 x 32 tiles,
+    // whose loads take longer than their MFMAs, still finish sooner
+    const bool vec = aligned16(A) && aligned16(B) && lda % 4 == 0 && ldb % 4 == 0 && K % 4 == 0;
+    const int64_t t64 = ceil_div(M, 64) * ceil_div(N, 64), t32 = ceil_div(M, 32) * ceil_div(N, 32);
+    if (4 * t64 >= 3 * kCus) {
+        if (vec)
+            hipLaunchKernelGGL((gemm_nt_f32<64, 64, 4, 4, true, Epi>), dim3((unsigned)t64), dim3(256), 0, st, A, lda, M, B,
+                               ldb, N, K, epi);
+        else
+            hipLaunchKernelGGL((gemm_nt_f32<64, 64, 4, 4, false, Epi>), dim3((unsigned)t64), dim3(256), 0, st, A, lda, M,
+                               B, ldb, N, K, epi);
+    } else {
+        if (vec)
+            hipLaunchKernelGGL((gemm_nt_f32<32, 32, 2, 8, true, Epi>), dim3((unsigned)t32), dim3(256), 0, st, A, lda, M, B,
+                               ldb, N, K, epi);
+        else
+            hipLaunchKernelGGL((gemm_nt_f32<32, 32, 2, 8, false, Epi>), dim3((unsigned)t32), dim3(256), 0, st, A, lda, M,
+                               B, ldb, N, K, epi);
+    }
     return hipGetLastError();
 }
 
@@ -621,7 +639,7 @@ pifa_status check_rows_aligned(pifa_dtype dt, int64_t d_in) {
 
 // ===================================================================== handles
 // bf16 layers keep their weights in lane order (layout.hpp); fp32 layers keep
-// row-major copies for the vector-ALU kernels.
+// row-major copies.
 struct pifa_layer {
     int device = 0;
     pifa_dtype dtype = PIFA_BF16;

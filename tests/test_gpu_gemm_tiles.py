@@ -124,3 +124,24 @@ def test_backward_column_split(d_out, r, M):
     assert np.all(np.abs(dC.cpu().numpy() - ref) <= bound + 1e-30)
     ref = Gp @ Wd
     assert np.linalg.norm(from_dev(dX) - ref) <= 2.0 ** -8 * np.linalg.norm(np.abs(Gp) @ np.abs(Wd))
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 17, 1), (31, 33, 5), (64, 64, 32), (33, 31, 100),  # 32 x 32 tiles, rows of any alignment
+    (1025, 1023, 36), (1031, 1017, 61),                    # 64 x 64 tiles, 16-byte and 4-byte loads
+])
+def test_f32_tile_edges(M, N, K):
+    torch = torch_mod()
+    from paper_2501_19090_amd import pifa
+    g = torch.Generator().manual_seed(11)
+    X, W = torch.randn(M, K, generator=g), torch.randn(N, K, generator=g)
+    X[5::97] = float("inf")
+    y = torch.full((M, N), float("nan"), device="cuda:0")
+    pifa.dense_forward(W.to("cuda:0"), X.to("cuda:0"), y)
+    torch.cuda.synchronize()
+    rows = np.setdiff1d(np.arange(M), np.arange(5, M, 97))
+    a, b = X.double().numpy()[rows], W.double().numpy()
+    bound = (K + 1) * U32 * (np.abs(a) @ np.abs(b).T)
+    got = from_dev(y)
+    assert np.all(np.abs(got[rows] - a @ b.T) <= bound)
+    assert not np.any(np.isfinite(got[5::97]))
