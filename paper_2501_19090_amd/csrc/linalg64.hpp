@@ -5,20 +5,27 @@
 //
 //   gemm64        C = alpha op(A) op(B) + beta C with arbitrary element strides
 //                 (transposes are strides, no copies) on fp64 MFMA tiles;
-//                 optional lower-triangle tiles only, for symmetric updates.
-//   Cholesky      A = L L^T, right-looking in 64-column blocks: diagonal block
-//                 in one workgroup's LDS, panel by forward substitution, trailing
-//                 update by gemm64 (lower tiles only).
+//                 optional lower-triangle tiles only, for symmetric results;
+//                 optionally a batch of equal products.
+//   Cholesky      A = L L^T, right-looking in blocks of 256 columns, each
+//                 factored 64 columns at a time: diagonal block in one
+//                 workgroup's registers (which also gives its inverse), panel
+//                 as a product with that inverse, the update of the block's
+//                 own columns, and one 256-deep update of the rest.
 //   spd solve     L L^T X = B for many right-hand sides: blocked forward and
-//                 backward substitution; each diagonal block is applied as its
-//                 explicit inverse (tri_inv_blocks), so every step is a gemm64.
+//                 backward substitution; each 256-wide diagonal block is
+//                 applied as its explicit inverse (put together from the
+//                 64-wide ones), so every step is a gemm64 at least 256 deep.
+// Updates 64 columns deep moved the trailing matrix for every 64 columns
+// and took half of the solve's time.
 #pragma once
 
 #include "common.hpp"
 
 namespace pifa {
 
-constexpr int kG64 = 64;  // block size of the factorisations and solves
+constexpr int kG64 = 64;    // columns factored at a time
+constexpr int kB64 = 256;   // block size of the trailing updates and solves
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -33,17 +40,30 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // unit-stride.  MFMA lane layout: lane l supplies A[l % 16][l / 16] and
 // B[l / 16][l % 16]; element v of the result is D[4 v + l / 16][l % 16].
 // Each output is one fp64 FMA chain over k in ascending order.
-// Grid: (ceil(Nc / BT), ceil(Mr / BT)).
+// C may be A where every workgroup writes only the rows it reads (Nc <= BT).
+// Grid: (ceil(Nc / BT), ceil(Mr / BT), batch).
+struct Batch64 {
+    // product z is at element offsets (z / per) * hi + (z % per) * lo
+    int n = 1, per = 1;
+    int64_t a_hi = 0, a_lo = 0, b_hi = 0, b_lo = 0, c_hi = 0, c_lo = 0;
+};
+
 template <int BT, int BK>
-__global__ __launch_bounds__(1024) void gemm64(int64_t Mr, int64_t Nc, int64_t K, double alpha,
-                                               const double* __restrict__ A, int64_t sa0, int64_t sa1,
-                                               const double* __restrict__ B, int64_t sb0, int64_t sb1, double beta,
-                                               double* __restrict__ C, int64_t sc0, int64_t sc1, int lower) {
+__global__ __launch_bounds__(1024) void gemm64(int64_t Mr, int64_t Nc, int64_t K, double alpha, const double* A,
+                                               int64_t sa0, int64_t sa1, const double* __restrict__ B, int64_t sb0,
+                                               int64_t sb1, double beta, double* C, int64_t sc0, int64_t sc1,
+                                               int lower, Batch64 bt) {
     constexpr int NT = 1024, LD = BT + 1, PT = BT * BK / NT;
     constexpr int WT = BT / 4, TT = WT / 16;
     static_assert(PT >= 1 && BT * BK % NT == 0 && WT % 16 == 0 && BK % 4 == 0, "bad fp64 tile");
     const int64_t i0 = (int64_t)blockIdx.y * BT, j0 = (int64_t)blockIdx.x * BT;
     if (lower && j0 > i0) return;
+    {
+        const int64_t hi = blockIdx.z / bt.per, lo = blockIdx.z % bt.per;
+        A += hi * bt.a_hi + lo * bt.a_lo;
+        B += hi * bt.b_hi + lo * bt.b_lo;
+        C += hi * bt.c_hi + lo * bt.c_lo;
+    }
     __shared__ double As[2][BK * LD];
     __shared__ double Bs[2][BK * LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -58,26 +78,40 @@ __global__ __launch_bounds__(1024) void gemm64(int64_t Mr, int64_t Nc, int64_t K
         jj = b_j1 ? e % BT : e / BK;
         kb = b_j1 ? e / BT : e % BK;
     };
+    // this thread's elements: source pointers (a valid one where the row or
+    // column is out of range) that step with K, LDS offsets
+    const double *pa[PT], *pb[PT];
+    int la[PT], lb[PT], ka[PT], kb_[PT];
+    bool oka[PT], okb[PT];
+#pragma unroll
+    for (int q = 0; q < PT; ++q) {
+        int ii, kk, kb, jj;
+        a_at(tid + NT * q, ii, kk);
+        b_at(tid + NT * q, kb, jj);
+        oka[q] = i0 + ii < Mr;
+        okb[q] = j0 + jj < Nc;
+        pa[q] = A + (oka[q] ? i0 + ii : 0) * sa0 + kk * sa1;
+        pb[q] = B + kb * sb0 + (okb[q] ? j0 + jj : 0) * sb1;
+        ka[q] = kk;
+        kb_[q] = kb;
+        la[q] = kk * LD + ii;
+        lb[q] = kb * LD + jj;
+    }
     double ra[PT], rb[PT];
     auto gload = [&](int64_t k0) {
 #pragma unroll
         for (int q = 0; q < PT; ++q) {
-            int ii, kk, kb, jj;
-            a_at(tid + NT * q, ii, kk);
-            b_at(tid + NT * q, kb, jj);
-            const int64_t i = i0 + ii, ka = k0 + kk, j = j0 + jj, kB = k0 + kb;
-            ra[q] = (i < Mr && ka < K) ? A[i * sa0 + ka * sa1] : 0.0;
-            rb[q] = (j < Nc && kB < K) ? B[kB * sb0 + j * sb1] : 0.0;
+            ra[q] = (oka[q] && k0 + ka[q] < K) ? *pa[q] : 0.0;
+            rb[q] = (okb[q] && k0 + kb_[q] < K) ? *pb[q] : 0.0;
+            pa[q] += BK * sa1;
+            pb[q] += BK * sb0;
         }
     };
     auto sstore = [&](int buf) {
 #pragma unroll
         for (int q = 0; q < PT; ++q) {
-            int ii, kk, kb, jj;
-            a_at(tid + NT * q, ii, kk);
-            b_at(tid + NT * q, kb, jj);
-            As[buf][kk * LD + ii] = ra[q];
-            Bs[buf][kb * LD + jj] = rb[q];
+            As[buf][la[q]] = ra[q];
+            Bs[buf][lb[q]] = rb[q];
         }
     };
     f64x4 acc[TT][TT];
@@ -143,185 +177,99 @@ __global__ __launch_bounds__(256) void pivot_floor64(const double* __restrict__ 
     if (threadIdx.x == 0) *out = kPivotTol * red[0];
 }
 
-// Unblocked Cholesky of the nb x nb (nb <= 64) block at A (row stride ld), in
-// place (lower triangle; the upper part is left as is).  One workgroup of 256
-// threads, block staged in LDS; thread (ty, tx) of a 16 x 16 grid owns rows
-// ty + 16a and columns tx + 16b (a, b < 4) of the trailing update, so no
-// index is divided.  Step j: every thread reads the pivot and the column
-// values it needs, a barrier, then the scaled column and the rank-1 update
-// are written.  *info is set to 1 on a pivot that is not finite or not above
-// *floor (the matrix is not numerically positive definite).
+// Cholesky of the nb x nb (nb <= 64) block at A (row stride ld), in place
+// (lower triangle; the upper part is neither read nor written), and the
+// inverse of the factor into Linv (row stride ldi, 64 x 64, zero above the
+// diagonal, identity past nb).
+// One workgroup of 256 threads; thread (ty, tx) of a 16 x 16 grid holds rows
+// ty + 16a and columns tx + 16b (a, b < 4) of the block and of an identity
+// matrix in registers.  Step j eliminates column j below the diagonal from
+// both, without square roots (A = L D L^T first): the owners of column j and
+// of the identity's row j publish them in LDS (alternating buffers), one
+// barrier, and every thread reads the pivot and its rows' and columns' values
+// and updates its 32 elements.  The identity becomes the unit factor's
+// inverse; square roots of the pivots scale both at the end.  Bound: the
+// latency of 64 dependent steps (LDS, barrier, division); the two-barrier
+// form with the block in LDS and a square root per step took 46 us (this 30),
+// and the inverses 23 us in a kernel of their own.
+// *info is set to 1 on a pivot that is not finite or not above *floor (the
+// matrix is not numerically positive definite).
 __global__ __launch_bounds__(256) void chol_diag(double* __restrict__ A, int64_t ld, int nb,
-                                                 const double* __restrict__ floor, int* __restrict__ info) {
-    __shared__ double L[kG64][kG64 + 1];
+                                                 const double* __restrict__ floor, int* __restrict__ info,
+                                                 double* __restrict__ Linv, int64_t ldi) {
+    __shared__ double col[2][kG64], row[2][kG64], piv[kG64];
     const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    {  // thread t loads column t % 64 of rows t / 64 + 4 k: 16 independent loads
-        const int c = tid % kG64, r0 = tid / kG64;
+    double a[4][4], e[4][4];
 #pragma unroll
-        for (int k = 0; k < kG64 / 4; ++k) {
-            const int i = r0 + 4 * k;
-            if (i < nb && c < nb) L[i][c] = A[(int64_t)i * ld + c];
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = ty + 16 * p, c = tx + 16 * q;
+            const bool in = c <= i && i < nb;
+            const double v = A[in ? (int64_t)i * ld + c : 0];  // in bounds, no branch
+            e[p][q] = i == c ? 1.0 : 0.0;
+            a[p][q] = in ? v : e[p][q];
         }
-    }
-    __syncthreads();
     const double fl = *floor;
-    for (int j = 0; j < nb; ++j) {
-        const double d = L[j][j];
-        const bool ok = d > fl && d > 0.0 && __builtin_isfinite(d);
-        const double s = ok ? sqrt(d) : 1.0;
-        const double inv = 1.0 / s;  // one division per step; the column is scaled by multiplication
-        double li[4], lc[4];
+    bool bad = false;
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            li[a] = L[ty + 16 * a][j] * inv;
-            lc[a] = L[tx + 16 * a][j] * inv;
-        }
-        const double cj = tid > j && tid < nb ? L[tid][j] * inv : 0.0;
-        __syncthreads();
-        if (tid == 0) {
-            L[j][j] = s;
-            if (!ok) *info = 1;
-        }
-        if (tid > j && tid < nb) L[tid][j] = cj;
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int i = ty + 16 * a, c = tx + 16 * b;
-                if (c > j && c <= i && i < nb) L[i][c] -= li[a] * lc[b];
-            }
-        __syncthreads();
-    }
-    {
-        const int c = tid % kG64, r0 = tid / kG64;
-#pragma unroll
-        for (int k = 0; k < kG64 / 4; ++k) {
-            const int i = r0 + 4 * k;
-            if (i < nb && c <= i) A[(int64_t)i * ld + c] = L[i][c];
-        }
-    }
-}
-
-constexpr int kWin = 8;  // columns per pass of the windowed substitution
-
-// Loads the nb x nb lower block at Ld (row stride ld) into rows [0, 64) of
-// L, zero everywhere else (columns >= nb, rows >= nb up to 127), and the
-// reciprocals of its diagonal into inv (zero past nb).  One wave, lane t
-// loading column t (coalesced loads, all in flight at once); the caller
-// synchronises.
-__device__ __forceinline__ void load_lower_block(const double* __restrict__ Ld, int64_t ld, int nb,
-                                                 double (&L)[2 * kG64][kG64 + 1], double (&inv)[kG64]) {
-    const int t = threadIdx.x;
-    const bool col_ok = t < nb;
-#pragma unroll
-    for (int i = 0; i < kG64; ++i) {
-        const double v = Ld[(int64_t)(i < nb ? i : 0) * ld + (col_ok ? t : 0)];  // in bounds, no branch
-        L[i][t] = (i < nb && col_ok) ? v : 0.0;
-    }
-#pragma unroll
-    for (int i = kG64; i < 2 * kG64; ++i) L[i][t] = 0.0;
-    inv[t] = t < nb ? 1.0 / Ld[(int64_t)t * ld + t] : 0.0;
-}
-
-// Forward substitution x <- L^-1 x for the lower block in LDS (as
-// load_lower_block leaves it), one right-hand side per lane in w.  Columns
-// are eliminated kWin at a time, each against every later row (the rows past
-// the block read the zero padding); after a pass the kWin finished values
-// go to out(j, value) and the window shifts down by kWin.  The loop body is
-// the same for every pass, so its code stays in the instruction cache (a
-// fully unrolled elimination is about 58 KB of straight-line code that each
-// wave fetches once).  Each pass runs as (column, 16-row chunk) steps whose
-// LDS reads are issued one step ahead of their FMAs, so the read latency
-// hides behind the previous step (38 -> 24 us for a 4032-row panel).
-template <typename Out>
-__device__ __forceinline__ void lower_solve_window(const double (&L)[2 * kG64][kG64 + 1], const double (&inv)[kG64],
-                                                   double (&w)[kG64], Out&& out) {
-    constexpr int kSteps = kWin * 4;  // (column t, chunk c) = (s / 4, s % 4)
+    for (int jb = 0; jb < 4; ++jb) {
 #pragma unroll 1
-    for (int j0 = 0; j0 < kG64; j0 += kWin) {
-        double buf[2][16];
-        auto load = [&](int s, double (&dst)[16]) {
-            const int t = s >> 2, c = s & 3;
+        for (int jj = 0; jj < 16; ++jj) {
+            const int j = 16 * jb + jj, buf = j & 1;
+            if (tx == jj)
 #pragma unroll
-            for (int ii = 0; ii < 16; ++ii) dst[ii] = L[j0 + 16 * c + ii][j0 + t];
-        };
-        load(0, buf[0]);
-        double xt = 0.0;
+                for (int p = 0; p < 4; ++p) col[buf][ty + 16 * p] = a[p][jb];
+            if (ty == jj)
 #pragma unroll
-        for (int s = 0; s < kSteps; ++s) {
-            const int t = s >> 2, c = s & 3;
-            if (s + 1 < kSteps) load(s + 1, buf[(s + 1) & 1]);
-            if (c == 0) {
-                xt = w[t] * inv[j0 + t];
-                w[t] = xt;
+                for (int q = 0; q < 4; ++q) row[buf][tx + 16 * q] = e[jb][q];
+            __syncthreads();
+            const double d = col[buf][j];
+            const bool ok = j >= nb || (d > fl && d > 0.0 && __builtin_isfinite(d));
+            bad |= !ok;
+            const double dd = ok ? d : 1.0;
+            if (tid == 0) piv[j] = dd;
+            const double inv = 1.0 / dd;
+            double f[4], lc[4], er[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) {
+                const int i = ty + 16 * p, c = tx + 16 * p;
+                f[p] = i > j ? col[buf][i] * inv : 0.0;
+                lc[p] = c > j ? col[buf][c] : 0.0;
+                er[p] = row[buf][c];
             }
 #pragma unroll
-            for (int ii = 0; ii < 16; ++ii) {
-                const int i = 16 * c + ii;
-                if (i > t) w[i] -= buf[s & 1][ii] * xt;
-            }
-            // keeps the scheduler from hoisting every read of the pass above
-            // the first FMA (hundreds of registers)
-            __builtin_amdgcn_sched_barrier(0);
+            for (int p = 0; p < 4; ++p)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (q <= p) a[p][q] -= f[p] * lc[q];
+                    if (q <= p) e[p][q] -= f[p] * er[q];
+                }
         }
-#pragma unroll
-        for (int t = 0; t < kWin; ++t) out(j0 + t, w[t]);
-#pragma unroll
-        for (int i = 0; i < kG64 - kWin; ++i) w[i] = w[i + kWin];
-#pragma unroll
-        for (int i = kG64 - kWin; i < kG64; ++i) w[i] = 0.0;
     }
-}
-
-// Panel of a blocked Cholesky: rows [0, nrows) of P (row stride ld, 64
-// columns) become P L11^-T, L11 being the 64 x 64 lower factor at Ld (row
-// stride ld): row p solves L11 x = p^T.  One row per lane.  Only full
-// diagonal blocks have a panel below them (a block narrower than 64 is the
-// last one of its matrix).
-__global__ __launch_bounds__(64) void chol_panel(const double* __restrict__ Ld, double* __restrict__ P, int64_t ld,
-                                                 int64_t nrows) {
-    __shared__ double L[2 * kG64][kG64 + 1];
-    __shared__ double inv[kG64];
-    load_lower_block(Ld, ld, kG64, L, inv);
     __syncthreads();
-    const int64_t row = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    if (row >= nrows) return;
-    double* p = P + row * ld;
-    double w[kG64];
-#pragma unroll
-    for (int j = 0; j < kG64; ++j) w[j] = p[j];
-    lower_solve_window(L, inv, w, [&](int j, double v) { p[j] = v; });
-}
-
-// Inverses of the diagonal blocks of a lower factor: block b (rows and
-// columns [64 b, 64 b + nb)) of the n x n factor L (row stride ld) goes to
-// Linv[b * 64 * 64 ...] as a dense 64 x 64 row-major block, zero above the
-// diagonal and outside nb x nb.  One one-wave workgroup per block; lane t
-// solves L_bb y = e_t, column t of the inverse.
-__global__ __launch_bounds__(64) void tri_inv_blocks(const double* __restrict__ L, int64_t ld, int64_t n,
-                                                     double* __restrict__ Linv) {
-    __shared__ double Ls[2 * kG64][kG64 + 1];
-    __shared__ double inv[kG64];
-    const int64_t kb = (int64_t)blockIdx.x * kG64;
-    const int nb = (int)(n - kb < kG64 ? n - kb : kG64);
-    load_lower_block(L + kb * ld + kb, ld, nb, Ls, inv);
+    if (bad && tid == 0) *info = 1;
+    if (tid < kG64) piv[tid] = sqrt(piv[tid]);
     __syncthreads();
-    const int t = threadIdx.x;
-    double w[kG64];
 #pragma unroll
-    for (int i = 0; i < kG64; ++i) w[i] = (i == t && t < nb) ? 1.0 : 0.0;
-    double* out = Linv + (int64_t)blockIdx.x * kG64 * kG64;
-    lower_solve_window(Ls, inv, w, [&](int j, double v) { out[j * kG64 + t] = v; });
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = ty + 16 * p, c = tx + 16 * q;
+            if (c <= i && i < nb) A[(int64_t)i * ld + c] = i == c ? piv[i] : a[p][q] / piv[c];
+            Linv[i * ldi + c] = c <= i ? e[p][q] / piv[i] : 0.0;
+        }
 }
 
-// out = a * X + b * Y + d * I (n x n row-major; Y may be null, then b is ignored)
-__global__ void axpby_diag64(int64_t n, double a, const double* __restrict__ X, double b, const double* __restrict__ Y,
-                             double d, double* __restrict__ out) {
-    const int64_t total = n * n;
+// out = a * X + b * Y + d * I (m x n row-major; Y may be null, then b is
+// ignored; out may be X or Y)
+__global__ void axpby_diag64(int64_t m, int64_t n, double a, const double* X, double b, const double* Y, double d,
+                             double* out) {
+    const int64_t total = m * n;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         double v = a * X[e];
         if (Y) v += b * Y[e];
-        if (e / n == e % n) v += d;
+        if (d != 0.0 && e / n == e % n) v += d;
         out[e] = v;
     }
 }

@@ -1499,72 +1499,113 @@ namespace {
 
 hipError_t gemm64_launch(hipStream_t st, int64_t Mr, int64_t Nc, int64_t K, double alpha, const double* A, int64_t sa0,
                          int64_t sa1, const double* B, int64_t sb0, int64_t sb1, double beta, double* C, int64_t sc0,
-                         int64_t sc1, bool lower = false) {
-    if (Mr <= 0 || Nc <= 0) return hipSuccess;
+                         int64_t sc1, bool lower = false, const Batch64& bt = Batch64{}) {
+    if (Mr <= 0 || Nc <= 0 || bt.n <= 0) return hipSuccess;
     // 128 x 128 tiles when they fill the chip and K is deep (about 60
     // TFLOP/s on the 4096-sized products, against 55 with 64 x 64 tiles);
-    // 64 x 64 tiles otherwise, e.g. the blocked updates with K = 64
-    if (!lower && K >= 512 && ceil_div(Mr, (int64_t)128) * ceil_div(Nc, (int64_t)128) >= kCus)
-        hipLaunchKernelGGL((gemm64<128, 8>), dim3((unsigned)ceil_div(Nc, (int64_t)128), (unsigned)ceil_div(Mr, (int64_t)128)),
-                           dim3(1024), 0, st, Mr, Nc, K, alpha, A, sa0, sa1, B, sb0, sb1, beta, C, sc0, sc1, 0);
+    // 64 x 64 tiles otherwise
+    const int64_t tm = ceil_div(Mr, (int64_t)128), tn = ceil_div(Nc, (int64_t)128);
+    const int64_t tiles = lower ? tm * (tm + 1) / 2 : tm * tn;
+    if (K >= kB64 && tiles * bt.n >= kCus)
+        hipLaunchKernelGGL((gemm64<128, 8>), dim3((unsigned)tn, (unsigned)tm, (unsigned)bt.n), dim3(1024), 0, st, Mr, Nc,
+                           K, alpha, A, sa0, sa1, B, sb0, sb1, beta, C, sc0, sc1, lower ? 1 : 0, bt);
     else
-        hipLaunchKernelGGL((gemm64<64, 16>), dim3((unsigned)ceil_div(Nc, (int64_t)64), (unsigned)ceil_div(Mr, (int64_t)64)),
+        hipLaunchKernelGGL((gemm64<64, 16>),
+                           dim3((unsigned)ceil_div(Nc, (int64_t)64), (unsigned)ceil_div(Mr, (int64_t)64), (unsigned)bt.n),
                            dim3(1024), 0, st, Mr, Nc, K, alpha, A, sa0, sa1, B, sb0, sb1, beta, C, sc0, sc1,
-                           lower ? 1 : 0);
+                           lower ? 1 : 0, bt);
     return hipGetLastError();
 }
+
+// Doubles of the inverted diagonal blocks of an n x n factor, and of the
+// scratch that puts them together.
+inline int64_t linv_elems(int64_t n) { return ceil_div(n, (int64_t)kB64) * (kB64 * kB64 + kB64 / 2 * kB64 / 2); }
 
 // In-place lower Cholesky of the n x n matrix A (row stride ld); *info set on
 // failure.  floor: one device double of scratch for the pivot threshold.
-hipError_t cholesky64(double* A, int64_t n, int64_t ld, double* floor, int* info, hipStream_t st) {
+// Linv (linv_elems(n) doubles): the inverse of each 256 x 256 diagonal block
+// of the factor, row-major; of a last, narrower block only the inverses of
+// its 64 x 64 diagonal blocks.
+hipError_t cholesky64(double* A, int64_t n, int64_t ld, double* Linv, double* floor, int* info, hipStream_t st) {
     hipLaunchKernelGGL(pivot_floor64, dim3(1), dim3(256), 0, st, (const double*)A, n, ld, floor);
-    for (int64_t kb = 0; kb < n; kb += kG64) {
-        const int nb = (int)std::min<int64_t>(kG64, n - kb);
-        double* Akk = A + kb * ld + kb;
-        hipLaunchKernelGGL(chol_diag, dim3(1), dim3(256), 0, st, Akk, ld, nb, (const double*)floor, info);
-        const int64_t rest = n - kb - nb;
-        if (rest > 0) {
-            double* L21 = A + (kb + nb) * ld + kb;
+    hipError_t e = hipMemsetAsync(Linv, 0, (size_t)(ceil_div(n, (int64_t)kB64) * kB64 * kB64) * 8, st);
+    for (int64_t b0 = 0; b0 < n && e == hipSuccess; b0 += kB64) {
+        const int64_t bw = std::min<int64_t>(kB64, n - b0);
+        double* Lb = Linv + (b0 / kB64) * kB64 * kB64;
+        for (int64_t j = 0; j < bw && e == hipSuccess; j += kG64) {
+            const int64_t kb = b0 + j, nb = std::min<int64_t>(kG64, n - kb), rest = n - kb - nb;
+            double* Akk = A + kb * ld + kb;
+            double* Li = Lb + j * (kB64 + 1);
+            hipLaunchKernelGGL(chol_diag, dim3(1), dim3(256), 0, st, Akk, ld, (int)nb, (const double*)floor, info, Li,
+                               (int64_t)kB64);
             // rest > 0: this block is a full one (nb == 64)
-            hipLaunchKernelGGL(chol_panel, dim3((unsigned)ceil_div(rest, (int64_t)64)), dim3(64), 0, st, Akk, L21, ld,
-                               rest);
-            hipError_t e = gemm64_launch(st, rest, rest, nb, -1.0, L21, ld, 1, L21, 1, ld, 1.0,
-                                         A + (kb + nb) * ld + kb + nb, ld, 1, true);
-            if (e != hipSuccess) return e;
+            double* A21 = Akk + nb * ld;
+            e = gemm64_launch(st, rest, nb, nb, 1.0, A21, ld, 1, Li, 1, kB64, 0.0, A21, ld, 1);
+            if (e == hipSuccess)  // the block's own columns
+                e = gemm64_launch(st, rest, bw - j - nb, nb, -1.0, A21, ld, 1, A21, 1, ld, 1.0, A21 + nb, ld, 1);
         }
+        const int64_t rest = n - b0 - bw;
+        double* A21 = A + (b0 + bw) * ld + b0;
+        if (e == hipSuccess)
+            e = gemm64_launch(st, rest, rest, bw, -1.0, A21, ld, 1, A21, 1, ld, 1.0, A21 + bw, ld, 1, true);
     }
-    return hipGetLastError();
+    // put the inverses of the whole 256-wide blocks together: the lower left
+    // quarter of [L11 0; L21 L22]^-1 is -L22^-1 L21 L11^-1
+    const int full = (int)(n / kB64);
+    double* T = Linv + ceil_div(n, (int64_t)kB64) * kB64 * kB64;
+    for (int64_t h = kG64; h < kB64 && e == hipSuccess; h *= 2) {
+        Batch64 bt;
+        bt.per = (int)(kB64 / (2 * h));
+        bt.n = full * bt.per;
+        bt.a_hi = kB64 * (ld + 1);  // L21
+        bt.a_lo = 2 * h * (ld + 1);
+        bt.b_hi = kB64 * kB64;  // L11^-1
+        bt.b_lo = 2 * h * (kB64 + 1);
+        bt.c_hi = kB64 / 2 * kB64 / 2;
+        bt.c_lo = h * h;
+        e = gemm64_launch(st, h, h, h, 1.0, A + h * ld, ld, 1, Linv, kB64, 1, 0.0, T, h, 1, false, bt);
+        bt.a_hi = bt.b_hi;  // L22^-1
+        bt.a_lo = bt.b_lo;
+        std::swap(bt.b_hi, bt.c_hi);
+        std::swap(bt.b_lo, bt.c_lo);
+        if (e == hipSuccess)
+            e = gemm64_launch(st, h, h, h, -1.0, Linv + h * (kB64 + 1), kB64, 1, T, h, 1, 0.0, Linv + h * kB64, kB64, 1,
+                              false, bt);
+    }
+    return e;
 }
 
 // B (n x nrhs, row stride ldb) <- (L L^T)^-1 B for the lower factor L (row
-// stride ld).  Linv: ceil(n / 64) * 64 * 64 doubles of scratch for the
-// inverted diagonal blocks; X: n * nrhs doubles of scratch (row stride nrhs).
+// stride ld) and Linv as cholesky64 leaves them.  X: n * nrhs doubles of
+// scratch (row stride nrhs).
 // Forward, L Y = B into X: Y_k = L_kk^-1 B_k, then the rows below lose
 // L_ik Y_k.  Backward, L^T Z = Y into B: Z_k = L_kk^-T Y_k, then the rows
-// above lose L_ki^T Z_k.  Multiplying by the inverted 64 x 64 blocks instead
-// of substituting keeps every step on the MFMA GEMM; the blocks of a
-// Cholesky factor of a matrix with condition number kappa have condition
-// numbers of at most sqrt(kappa), which bounds what the explicit inverses add
-// to the substitution's rounding error.
-hipError_t spd_solve64(const double* L, int64_t n, int64_t ld, double* B, int64_t nrhs, int64_t ldb, double* Linv,
-                       double* X, hipStream_t st) {
-    const int64_t nblk = ceil_div(n, (int64_t)kG64);
-    hipLaunchKernelGGL(tri_inv_blocks, dim3((unsigned)nblk), dim3(64), 0, st, L, ld, n, Linv);
-    hipError_t e = hipGetLastError();
-    for (int64_t kb = 0; kb < n && e == hipSuccess; kb += kG64) {
-        const int64_t nb = std::min<int64_t>(kG64, n - kb), rest = n - kb - nb;
-        const double* Li = Linv + (kb / kG64) * kG64 * kG64;
-        e = gemm64_launch(st, nb, nrhs, nb, 1.0, Li, kG64, 1, B + kb * ldb, ldb, 1, 0.0, X + kb * nrhs, nrhs, 1);
+// above lose L_ki^T Z_k.  Multiplying by the inverted blocks (256 wide; 64
+// wide in a last block that is narrower) instead of substituting keeps every
+// step on the MFMA GEMM; the diagonal blocks of a Cholesky factor of a matrix
+// with condition number kappa have condition numbers of at most sqrt(kappa),
+// which bounds what the explicit inverses add to the substitution's rounding
+// error.
+hipError_t spd_solve64(const double* L, int64_t n, int64_t ld, double* B, int64_t nrhs, int64_t ldb,
+                       const double* Linv, double* X, hipStream_t st) {
+    hipError_t e = hipSuccess;
+    // block of width w (256, or 64 inside a narrower last block) and its inverse
+    auto inverse = [&](int64_t kb) { return Linv + (kb / kB64) * kB64 * kB64 + (kb % kB64) * (kB64 + 1); };
+    const int64_t full = n / kB64 * kB64;
+    auto width = [&](int64_t kb) { return kb < full ? (int64_t)kB64 : std::min<int64_t>(kG64, n - kb); };
+    for (int64_t kb = 0; kb < n && e == hipSuccess; kb += width(kb)) {
+        const int64_t nb = width(kb), rest = n - kb - nb;
+        e = gemm64_launch(st, nb, nrhs, nb, 1.0, inverse(kb), kB64, 1, B + kb * ldb, ldb, 1, 0.0, X + kb * nrhs, nrhs, 1);
         if (e == hipSuccess)
             e = gemm64_launch(st, rest, nrhs, nb, -1.0, L + (kb + nb) * ld + kb, ld, 1, X + kb * nrhs, nrhs, 1, 1.0,
                               B + (kb + nb) * ldb, ldb, 1);
     }
-    for (int64_t kb = (nblk - 1) * kG64; kb >= 0 && e == hipSuccess; kb -= kG64) {
-        const int64_t nb = std::min<int64_t>(kG64, n - kb);
-        const double* Li = Linv + (kb / kG64) * kG64 * kG64;
-        e = gemm64_launch(st, nb, nrhs, nb, 1.0, Li, 1, kG64, X + kb * nrhs, nrhs, 1, 0.0, B + kb * ldb, ldb, 1);
+    for (int64_t end = n; end > 0 && e == hipSuccess;) {
+        const int64_t kb = end > full ? full + (end - 1 - full) / kG64 * kG64 : end - kB64, nb = end - kb;
+        e = gemm64_launch(st, nb, nrhs, nb, 1.0, inverse(kb), 1, kB64, X + kb * nrhs, nrhs, 1, 0.0, B + kb * ldb, ldb, 1);
         if (e == hipSuccess)
             e = gemm64_launch(st, kb, nrhs, nb, -1.0, L + kb * ld, 1, ld, B + kb * ldb, ldb, 1, 1.0, X, nrhs, 1);
+        end = kb;
     }
     return e;
 }
@@ -1705,7 +1746,7 @@ pifa_status pifa_calib_reconstruct(pifa_calib_handle c, const double* W, int64_t
     auto al = [](int64_t e) { return round_up(e, (int64_t)32); };
     const int64_t e_Z = al(n * n), e_T = al(m * n), e_SV = al(n * r), e_A = al(r * r), e_Bt = al(r * m),
                   e_G = al(r * r), e_H = al(r * n), e_QT = al(n * r), e_Sa = al(n * n),
-                  e_X = al(std::max(r * m, r * n)), e_Li = ceil_div(n, (int64_t)kG64) * kG64 * kG64;
+                  e_X = al(std::max(r * m, r * n)), e_Li = al(linv_elems(n));
     pifa_status s = c->work.ensure(
         (size_t)(e_Z + e_T + e_SV + e_A + e_Bt + e_G + e_H + e_QT + e_Sa + e_X + e_Li + 32) * 8, st);
     if (s != PIFA_OK) return s;
@@ -1731,30 +1772,31 @@ pifa_status pifa_calib_reconstruct(pifa_calib_handle c, const double* W, int64_t
     hipLaunchKernelGGL(symmetrize_lower64, dim3(grid_for(n * n)), dim3(256), 0, st, c->S, n);
     PIFA_GO(hipGetLastError());
     // T = W (lam P + (1 - lam) S)
-    hipLaunchKernelGGL(axpby_diag64, dim3(grid_for(n * n)), dim3(256), 0, st, n, lam, (const double*)c->P, 1.0 - lam,
+    hipLaunchKernelGGL(axpby_diag64, dim3(grid_for(n * n)), dim3(256), 0, st, n, n, lam, (const double*)c->P, 1.0 - lam,
                        (const double*)c->S, 0.0, Z);
     PIFA_GO(hipGetLastError());
     PIFA_GO(gemm64_launch(st, m, n, n, 1.0, W, n, 1, Z, n, 1, 0.0, T, n, 1));
-    // A_r = V^T S V with V = Vt^T;  (T V)^T
+    // A_r = V^T S V with V = Vt^T (symmetric: the lower tiles);  (T V)^T
     PIFA_GO(gemm64_launch(st, n, r, n, 1.0, c->S, n, 1, Vt, 1, n, 0.0, SV, r, 1));
-    PIFA_GO(gemm64_launch(st, r, r, n, 1.0, Vt, n, 1, SV, r, 1, 0.0, Ar, r, 1));
+    PIFA_GO(gemm64_launch(st, r, r, n, 1.0, Vt, n, 1, SV, r, 1, 0.0, Ar, r, 1, true));
     PIFA_GO(gemm64_launch(st, r, m, n, 1.0, Vt, n, 1, T, 1, n, 0.0, Ut, m, 1));
-    // U_r^T = A_r^-1 (T V)^T   (A_r symmetric)
-    PIFA_GO(cholesky64(Ar, r, r, floor, c->info, st));
+    // U_r^T = A_r^-1 (T V)^T
+    PIFA_GO(cholesky64(Ar, r, r, Linv, floor, c->info, st));
     PIFA_GO(spd_solve64(Ar, r, r, Ut, m, m, Linv, X, st));
-    // G = U_r^T U_r;  H = U_r^T (T + a W)
-    PIFA_GO(gemm64_launch(st, r, r, m, 1.0, Ut, m, 1, Ut, 1, m, 0.0, G, r, 1));
+    // G = U_r^T U_r (lower tiles);  H = U_r^T (T + a W), the sum in T
+    PIFA_GO(gemm64_launch(st, r, r, m, 1.0, Ut, m, 1, Ut, 1, m, 0.0, G, r, 1, true));
+    hipLaunchKernelGGL(axpby_diag64, dim3(grid_for(m * n)), dim3(256), 0, st, m, n, alpha, W, 1.0, (const double*)T, 0.0, T);
+    PIFA_GO(hipGetLastError());
     PIFA_GO(gemm64_launch(st, r, n, m, 1.0, Ut, m, 1, T, n, 1, 0.0, H, n, 1));
-    PIFA_GO(gemm64_launch(st, r, n, m, alpha, Ut, m, 1, W, n, 1, 1.0, H, n, 1));
     // Q = G^-1 H
-    PIFA_GO(cholesky64(G, r, r, floor, c->info, st));
+    PIFA_GO(cholesky64(G, r, r, Linv, floor, c->info, st));
     PIFA_GO(spd_solve64(G, r, r, H, n, n, Linv, X, st));
     // V_r = (S + a I)^-1 Q^T  (n x r), i.e. V_r^T = Q (S + a I)^-1
-    hipLaunchKernelGGL(axpby_diag64, dim3(grid_for(n * n)), dim3(256), 0, st, n, 1.0, (const double*)c->S, 0.0,
+    hipLaunchKernelGGL(axpby_diag64, dim3(grid_for(n * n)), dim3(256), 0, st, n, n, 1.0, (const double*)c->S, 0.0,
                        (const double*)nullptr, alpha, Sa);
     PIFA_GO(hipGetLastError());
     PIFA_GO(transpose64_launch(H, r, n, QT, st));
-    PIFA_GO(cholesky64(Sa, n, n, floor, c->info, st));
+    PIFA_GO(cholesky64(Sa, n, n, Linv, floor, c->info, st));
     PIFA_GO(spd_solve64(Sa, n, n, QT, r, r, Linv, X, st));
     // outputs
     PIFA_GO(transpose64_launch(Ut, r, m, U_r, st));
