@@ -37,9 +37,17 @@ struct ALoad16 {
     int64_t lda;
     int64_t M;
     static constexpr int kOps = 1;
+    static constexpr bool kBuffered = true;  // has rsrc and its load
     __device__ __forceinline__ void load(int m, int64_t k, int64_t K, u32x4 (&out)[1]) const {
         out[0] = zero16();
         if (m < M && k < K) out[0] = *reinterpret_cast<const u32x4*>(a + (int64_t)m * lda + k);
+    }
+    // the same without branches, through a buffer resource
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(int64_t K) const {
+        return make_rsrc31(a, ((M - 1) * lda + K) * 2);
+    }
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int m, int k, int64_t K, u32x4 (&out)[1]) const {
+        out[0] = load16(rs, m < M && k < K ? (uint32_t)((m * lda + k) * 2) : kMaskedOffset);
     }
 };
 
@@ -50,6 +58,7 @@ struct ALoadPair16 {
     int64_t lda;
     int64_t M;
     static constexpr int kOps = 2;
+    static constexpr bool kBuffered = true;
     __device__ __forceinline__ void load(int m, int64_t k, int64_t K, u32x4 (&out)[2]) const {
         out[0] = zero16();
         out[1] = zero16();
@@ -57,6 +66,14 @@ struct ALoadPair16 {
             out[0] = *reinterpret_cast<const u32x4*>(a + (int64_t)m * lda + k);
             out[1] = *reinterpret_cast<const u32x4*>(a + (M + (int64_t)m) * lda + k);
         }
+    }
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(int64_t K) const {
+        return make_rsrc31(a, ((2 * M - 1) * lda + K) * 2);
+    }
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int m, int k, int64_t K, u32x4 (&out)[2]) const {
+        const bool ok = m < M && k < K;
+        out[0] = load16(rs, ok ? (uint32_t)((m * lda + k) * 2) : kMaskedOffset);
+        out[1] = load16(rs, ok ? (uint32_t)(((M + m) * lda + k) * 2) : kMaskedOffset);
     }
 };
 
@@ -70,6 +87,7 @@ struct ASplit32 {
     int64_t M;
     float scale;
     static constexpr int kOps = 2;
+    static constexpr bool kBuffered = false;
     __device__ __forceinline__ void load(int m, int64_t k, int64_t K, u32x4 (&out)[2]) const {
         f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
         if (m < M && k < K) {
@@ -371,6 +389,112 @@ __global__ __launch_bounds__(WAVES* kWave) void skinny_stream(SkinnyGroup<TB, AL
         step(cur, w1);
         cur = nxt;
         nxt = next(nxt);
+    }
+}
+
+// Long weight streams with more activation rows than skinny_stream takes,
+// whose MFMA operands fit the registers: one workgroup of 8 waves per CU, each
+// walking a contiguous range of the group's 16-row groups (units).
+// Wave w multiplies K blocks w, w + 8, ..., w + 8 (R - 1) of every unit, so
+// the operands of its activation rows are the same for all units of a
+// problem: they are loaded once, for any M <= 16, and the loop issues nothing
+// but weight loads, three passes ahead, across units and reductions.
+// (skinny_packed re-reads the activations for every 16 weight rows: at M = 8
+// the grouped non-pivot product of two 36.7 MB coefficient matrices took 21.0
+// us, 18.9 here; each group cut in two for balance 21.9.)  Bound: HBM.
+// With 16 waves and at most 4 rows the operands left no registers to prefetch
+// into, and skinny_stream stayed faster (67 MB in 12.5 against 20 us).
+// Sums in the order of skinny_packed with 8 waves (bit-identical).
+// Needs packed_kblocks(K) <= 8 R for every problem, and R * OPS <= 8.
+template <typename TB, int R, typename AL, typename Epi>
+__global__ __launch_bounds__(8 * kWave) void skinny_resident(SkinnyGroup<TB, AL, Epi> grp) {
+    constexpr int OPS = AL::kOps, WAVES = 8;
+    static_assert(R * OPS <= 8, "register budget");
+    // pass s of the walk is in buffer s % NB: NU units per trip make that a constant
+    constexpr int NB = 4, DEPTH = NB - 1, NU = NB > R ? NB / R : 1;
+    static_assert(NU * R % NB == 0, "whole turns of the buffers");
+    __shared__ f32x4 red[2][WAVES][kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int row = lane & 15;
+    const int units = (int)grp.start[grp.n];
+    const int u_end = (int)((int64_t)units * (blockIdx.x + 1) / gridDim.x);
+    int u = (int)((int64_t)units * blockIdx.x / gridDim.x);
+
+    // the problem of a unit, and what the weight loads need of it
+    struct Src {
+        int q, start, end, KB;
+        const TB* B;
+    };
+    auto source = [&](int v, int q) {
+        while (q + 1 < grp.n && v >= (int)grp.start[q + 1]) ++q;
+        return Src{q, (int)grp.start[q], (int)grp.start[q + 1], (int)packed_kblocks(grp.p[q].K), grp.p[q].B};
+    };
+    // weights of pass p of unit v (zeros past the end: a masked offset is
+    // past the buffer range)
+    auto fetch = [&](int v, int p, const Src& s, u32x4(&bw)[4]) {
+        const int lu = v - s.start, b = p * WAVES + wave;
+        const bool mine = v < u_end && b < s.KB;
+        const auto rs = make_rsrc31(s.B + (int64_t)lu * s.KB * (kPackChunks * 8), (int64_t)s.KB * kPackChunks * 16);
+        const uint32_t off = mine ? (uint32_t)((b * kPackChunks + lane) * 16) : kMaskedOffset;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) bw[c] = load16(rs, off + c * kWave * 16);
+    };
+    u32x4 a[R][4][OPS];
+    auto activations = [&](int q) {
+        const SkinnyProblem<TB, AL, Epi>& P = grp.p[q];
+        const auto rs = P.al.rsrc(P.K);
+#pragma unroll
+        for (int p = 0; p < R; ++p)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                P.al.load(rs, row, (p * WAVES + wave) * kSkinnyStepK + (lane >> 4) * 32 + c * 8, P.K, a[p][c]);
+        // everything has landed (vmcnt 0): left in flight, the loop would wait
+        // at every use of the operands, and with them for the prefetch
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+    };
+    Src src = source(u, 0), cur = src;  // of the unit being loaded, and multiplied
+    u32x4 w[NB][4];
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        if (d % R == 0 && u + d / R >= src.end && u + d / R < units) src = source(u + d / R, src.q);
+        fetch(u + d / R, d % R, src, w[d]);
+    }
+    activations(cur.q);
+    int par = 0;
+    while (true) {
+#pragma unroll
+        for (int k = 0; k < NU; ++k) {
+            if (u >= u_end) return;
+            if (u >= cur.end) {
+                cur = source(u, cur.q);
+                activations(cur.q);
+            }
+            f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int p = 0; p < R; ++p) {
+                const int v = u + (p + DEPTH) / R;
+                if ((p + DEPTH) % R == 0 && v >= src.end && v < units) src = source(v, src.q);
+                fetch(v, (p + DEPTH) % R, src, w[(k * R + p + DEPTH) % NB]);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+#pragma unroll
+                    for (int o = 0; o < OPS; ++o) acc = Mfma<TB>::mma16(a[p][c][o], w[(k * R + p) % NB][c], acc);
+            }
+            red[par][wave][lane] = acc;
+            __syncthreads();
+            if (wave == (u & (WAVES - 1))) {
+                f32x4 tot = red[par][0][lane];
+#pragma unroll
+                for (int x = 1; x < WAVES; ++x) tot += red[par][x][lane];
+                const Epi& epi = grp.p[cur.q].epi;
+                const auto c = epi.col((int64_t)(u - cur.start) * kSkinnyRows + row);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) epi.store(4 * (lane >> 4) + v, c, tot[v]);
+            }
+            par ^= 1;
+            ++u;
+        }
     }
 }
 

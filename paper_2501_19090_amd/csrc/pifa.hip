@@ -458,6 +458,28 @@ void skinny_stream_launch(SkinnyGroup<TB, AL, Epi> grp, int64_t k_blocks_total, 
                        grp);
 }
 
+// skinny_resident: more rows than skinny_stream takes, a stream as long with
+// at least two 16-row groups per CU (with one, the activations' round trip is
+// not hidden: a 33.5 MB pivot product of 256 groups 10.4 us against 9.2), and
+// operands that fit without spilling: passes over K at most 4, times operands
+// at most 8.  Launches and returns true if so.
+template <typename TB, typename AL, typename Epi>
+bool skinny_resident_launch(SkinnyGroup<TB, AL, Epi> grp, int64_t KB, int64_t blocks, hipStream_t st) {
+    constexpr int OPS = AL::kOps;
+    const int64_t M = grp.p[0].al.M, groups = grp.start[grp.n], passes = ceil_div(KB, (int64_t)8);
+    if (!AL::kBuffered || M <= kStreamRows || M > kDecodeMaxM || blocks < kStreamMinBlocks || groups < 2 * kCus || passes > 4 || passes * OPS > 8) return false;
+    const dim3 grid((unsigned)kCus);
+    auto go = [&](auto r) {
+        constexpr int R = decltype(r)::value;
+        if constexpr (AL::kBuffered && R * OPS <= 8)
+            hipLaunchKernelGGL((skinny_resident<TB, R, AL, Epi>), grid, dim3(8 * kWave), 0, st, grp);
+    };
+    if (passes <= 1) go(std::integral_constant<int, 1>{});
+    else if (passes <= 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 4>{});
+    return true;
+}
+
 // Whether a weight stream of `blocks` 16 x 128 blocks over k_blocks_total
 // staged K blocks takes the streaming kernel.
 inline bool use_stream(int64_t M, int64_t blocks, int64_t k_blocks_total, int ops) {
@@ -470,12 +492,13 @@ void skinny_packed_mt(const AL& al, const TB* B, int64_t N, int64_t K, const Epi
     const int64_t groups = packed_groups(N);
     if constexpr (MT == 1) {
         const int64_t KB = packed_kblocks(K);
+        SkinnyGroup<TB, AL, Epi> one;
+        one.p[0] = SkinnyProblem<TB, AL, Epi>{al, B, K, epi};
+        one.n = 1;
+        one.start[0] = 0;
+        one.start[1] = groups;
+        if (skinny_resident_launch(one, KB, groups * KB, st)) return;
         if (use_stream(al.M, groups * KB, KB, AL::kOps)) {
-            SkinnyGroup<TB, AL, Epi> one;
-            one.p[0] = SkinnyProblem<TB, AL, Epi>{al, B, K, epi};
-            one.n = 1;
-            one.start[0] = 0;
-            one.start[1] = groups;
             if (groups <= 128) return skinny_stream_launch<TB, 2>(one, KB, st);
             return skinny_stream_launch<TB, 1>(one, KB, st);
         }
@@ -526,6 +549,7 @@ hipError_t launch_skinny_grouped(int site, SkinnyGroup<TB, AL, Epi> grp, const i
         blocks += (grp.start[q + 1] - grp.start[q]) * packed_kblocks(grp.p[q].K);
     }
     TimedLaunch timed(site, st);
+    if (skinny_resident_launch(grp, KB, blocks, st)) return hipGetLastError();
     if (use_stream(grp.p[0].al.M, blocks, kb_total, AL::kOps)) {
         skinny_stream_launch<TB, 1>(grp, kb_total, st);
         return hipGetLastError();
