@@ -1530,7 +1530,9 @@ hipError_t gemm64_launch(hipStream_t st, int64_t Mr, int64_t Nc, int64_t K, doub
     // 64 x 64 tiles otherwise
     const int64_t tm = ceil_div(Mr, (int64_t)128), tn = ceil_div(Nc, (int64_t)128);
     const int64_t tiles = lower ? tm * (tm + 1) / 2 : tm * tn;
-    if (K >= kB64 && tiles * bt.n >= kCus)
+    // (a deep symmetric product that half fills the chip with 128 x 128 tiles,
+    // 2048 x 2048 x 4096: SYMA us, with 64 x 64 tiles 690)
+    if ((K >= kB64 && tiles * bt.n >= kCus) || (lower && K >= 1024 && 2 * tiles >= kCus))
         hipLaunchKernelGGL((gemm64<128, 8>), dim3((unsigned)tn, (unsigned)tm, (unsigned)bt.n), dim3(1024), 0, st, Mr, Nc,
                            K, alpha, A, sa0, sa1, B, sb0, sb1, beta, C, sc0, sc1, lower ? 1 : 0, bt);
     else
@@ -1751,10 +1753,10 @@ pifa_status pifa_calib_read(pifa_calib_handle c, double* S, double* P, void* str
     PIFA_ON_DEVICE(c->device);
     const size_t b = (size_t)c->n * c->n * sizeof(double);
     if (S) {
-        hipLaunchKernelGGL(symmetrize_lower64, dim3(grid_for(c->n * c->n)), dim3(256), 0, as_stream(stream), c->S, c->n);
+        const unsigned nt = (unsigned)ceil_div(c->n, (int64_t)32);
+        hipLaunchKernelGGL(complete_lower64, dim3(nt, nt), dim3(256), 0, as_stream(stream), (const double*)c->S, c->n, S);
         PIFA_HIP(hipGetLastError());
     }
-    if (S) PIFA_HIP(hipMemcpyAsync(S, c->S, b, hipMemcpyDeviceToDevice, as_stream(stream)));
     if (P) PIFA_HIP(hipMemcpyAsync(P, c->P, b, hipMemcpyDeviceToDevice, as_stream(stream)));
     return PIFA_OK;
 }
@@ -1793,7 +1795,8 @@ pifa_status pifa_calib_reconstruct(pifa_calib_handle c, const double* W, int64_t
         if ((e = (call)) != hipSuccess) return PIFA_ERR_HIP; \
     } while (0)
     PIFA_HIP(hipMemsetAsync(c->info, 0, sizeof(int), st));
-    hipLaunchKernelGGL(symmetrize_lower64, dim3(grid_for(n * n)), dim3(256), 0, st, c->S, n);
+    const unsigned nt = (unsigned)ceil_div(n, (int64_t)32);
+    hipLaunchKernelGGL(complete_lower64, dim3(nt, nt), dim3(256), 0, st, (const double*)c->S, n, c->S);
     PIFA_GO(hipGetLastError());
     // T = W (lam P + (1 - lam) S)
     hipLaunchKernelGGL(axpby_diag64, dim3(grid_for(n * n)), dim3(256), 0, st, n, n, lam, (const double*)c->P, 1.0 - lam,
