@@ -332,9 +332,18 @@ struct RowScaleEpi {
         if (m < M && c.ok) Store<bf16>::put(out + m * ldo + c.n, v * row_scale[m] * out_scale);
     }
     template <int W>
-    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
+    struct Old {
+        float scale;
+    };
+    template <int W>
+    __device__ __forceinline__ Old<W> old(int64_t m, int64_t n) const {
+        (void)n;
+        return Old<W>{row_scale[m < M ? m : 0]};
+    }
+    template <int W>
+    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W], const Old<W>& o) const {
         if (m >= M || n >= N) return;
-        const float s = row_scale[m];
+        const float s = o.scale;
         uint16_t h[W];
 #pragma unroll
         for (int x = 0; x < W; ++x) h[x] = f32_to_bf16_bits(v[x] * s * out_scale);

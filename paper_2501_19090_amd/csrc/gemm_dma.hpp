@@ -103,6 +103,17 @@ struct ScatterRowsT<ScatterEpi<bf16, WS>> {
     static constexpr bool value = true;
 };
 
+// An epilogue with old<W>(m, n) needs values from memory (sums to add to, a
+// row's scale): it loads a run's, which run takes, row blocks ahead.
+template <typename E, typename = void>
+struct OldEpi {
+    static constexpr bool value = false;
+};
+template <typename E>
+struct OldEpi<E, std::void_t<decltype(&E::template old<4>)>> {
+    static constexpr bool value = true;
+};
+
 // The LDS image of one operand's K tile of 64 (ROWS rows of the tile, 128
 // bytes each) in 1 KB pieces, one load instruction each; NI waves issue them,
 // wave iw piece iw, iw + NI, ...  WT: rows one wave of the product reads;
@@ -459,6 +470,30 @@ __device__ __forceinline__ void gemm_dma_tile(const T* __restrict__ A, int64_t l
 #pragma unroll
             for (int c = 0; c < C; ++c)
                 if (sdst[c] >= 0) y[sdst[c]] = h[c];
+        }
+    } else if constexpr (OldEpi<Epi>::value) {
+        constexpr int U = kDealt ? 1 : TN;
+        using Old = typename Epi::template Old<W>;
+        constexpr int D = sizeof(Old) <= 4 ? TM : 2;  // row blocks in flight
+        if (multiplies) {
+            Old o[D][U];
+            auto load = [&](int i) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) o[i % D][u] = epi.template old<W>(run_row(i), run_col(u));
+            };
+#pragma unroll
+            for (int i = 0; i < D - 1; ++i) load(i);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (i + D - 1 < TM) load(i + D - 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float v[W];
+                    run_vals(i, u, v);
+                    epi.template run<W>(run_row(i), run_col(u), v, o[i % D][u]);
+                }
+            }
         }
     } else if (multiplies) {
 #pragma unroll
