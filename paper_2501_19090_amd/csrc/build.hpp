@@ -18,7 +18,8 @@
 
 namespace pifa {
 
-constexpr int kBuildThreads = 1024;
+constexpr int kPivotThreads = 512;  // per workgroup of a pivot step
+constexpr int kPivotBlocks = 16;    // workgroups of a pivot step, at most
 
 // Cross-lane moves on the VALU (DPP) instead of the LDS crossbar that
 // __shfl_xor uses.  dpp<CTRL, ROWS>(x, old): lane l gets x from the lane CTRL
@@ -111,309 +112,241 @@ __device__ __forceinline__ void argmax_step(double& v, int32_t& k, int32_t& i) {
     }
 }
 
-// The pivot of step k, for a workgroup of kBuildThreads threads (all of them
+// The pivot of step k, for a workgroup of kPivotThreads threads (all of them
 // call it): the column c in [k, d_out) of largest norm2[c], ties to the
-// lowest original index perm[c].  The comparison is a total order, so the
-// result is exact whatever the reduction order.
+// lowest original index perm[c]; k where no norm compares (all NaN).  The
+// comparison is a total order, so every workgroup finds the same column.
+// Eight candidates are loaded at a time (clamped, so no branch per load), and
+// every wave folds the waves' results itself: one barrier.
 __device__ __forceinline__ int64_t block_pivot(const double* __restrict__ norm2, const int32_t* __restrict__ perm,
-                                               int64_t k, int64_t d_out, double* s_val, int64_t* s_idx,
+                                               int64_t k, int64_t d_out, double* s_val, int32_t* s_idx,
                                                int32_t* s_key) {
+    static_assert(kPivotThreads / kWave <= 16, "the waves' results are folded within a row of 16 lanes");
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     double bv = -1.0;
-    int64_t bi = -1;
-    int32_t bk = INT32_MAX;
-    for (int64_t c = k + tid; c < d_out; c += kBuildThreads) {
-        const double v = norm2[c];
-        const int32_t key = perm[c];
-        if (v > bv || (v == bv && key < bk)) {
-            bv = v;
-            bi = c;
-            bk = key;
+    int32_t bi = -1, bk = INT32_MAX;
+    for (int64_t c0 = k + tid; c0 < d_out; c0 += 8 * kPivotThreads) {
+        double v[8];
+        int32_t key[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int64_t c = min(c0 + u * kPivotThreads, d_out - 1);  // the last column again: no effect
+            v[u] = norm2[c];
+            key[u] = perm[c];
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (v[u] > bv || (v[u] == bv && key[u] < bk)) {
+                bv = v[u];
+                bi = (int32_t)min(c0 + u * kPivotThreads, d_out - 1);
+                bk = key[u];
+            }
     }
-    {   // the wave's best (value, key, index), on the VALU; a total order
-        // (larger value, then smaller key), so the result is exact
-        int32_t bi32 = (int32_t)bi;
-        argmax_step<0xB1, 0xF>(bv, bk, bi32);
-        argmax_step<0x4E, 0xF>(bv, bk, bi32);
-        argmax_step<0x124, 0xF>(bv, bk, bi32);
-        argmax_step<0x128, 0xF>(bv, bk, bi32);
-        argmax_step<0x142, 0xA>(bv, bk, bi32);
-        argmax_step<0x143, 0xC>(bv, bk, bi32);
-        bv = lane63(bv);
-        bk = __builtin_amdgcn_readlane(bk, 63);
-        bi = (int64_t)__builtin_amdgcn_readlane(bi32, 63);
-    }
-    if (lane == 0) {
+    argmax_step<0xB1, 0xF>(bv, bk, bi);
+    argmax_step<0x4E, 0xF>(bv, bk, bi);
+    argmax_step<0x124, 0xF>(bv, bk, bi);
+    argmax_step<0x128, 0xF>(bv, bk, bi);
+    argmax_step<0x142, 0xA>(bv, bk, bi);
+    argmax_step<0x143, 0xC>(bv, bk, bi);
+    if (lane == kWave - 1) {
         s_val[wave] = bv;
         s_idx[wave] = bi;
         s_key[wave] = bk;
     }
     __syncthreads();
-    if (tid == 0) {
-        for (int w = 1; w < kBuildThreads / kWave; ++w)
-            if (s_val[w] > bv || (s_val[w] == bv && s_key[w] < bk)) {
-                bv = s_val[w];
-                bi = s_idx[w];
-                bk = s_key[w];
-            }
-        s_idx[0] = bi;
-    }
-    __syncthreads();
-    return s_idx[0];
+    const int w = lane & (kPivotThreads / kWave - 1);
+    bv = s_val[w];
+    bi = s_idx[w];
+    bk = s_key[w];
+    argmax_step<0xB1, 0xF>(bv, bk, bi);
+    argmax_step<0x4E, 0xF>(bv, bk, bi);
+    argmax_step<0x124, 0xF>(bv, bk, bi);
+    argmax_step<0x128, 0xF>(bv, bk, bi);
+    const int64_t p = __builtin_amdgcn_readlane(bi, 63);
+    return p < k ? k : p;
 }
 
-// Step k = k0 + j, part 1 (a single workgroup of kBuildThreads threads):
-//   * pivot: the column of largest (downdated) residual norm, ties to the
-//     lowest original index; swap it into position k (A columns, F rows,
-//     norms, perm);
-//   * bring column k's rows [k, d_in) up to date: a_k -= V[:, 0:j] F[k, 0:j]^T;
-//   * turn a_k[k:] into a Householder reflector (R[k][k] on the diagonal,
-//     v[1:] below it, tau[k]);
-//   * aux[t] = -tau_k V[k:, t]^T v_k for t < j (for F's recurrence).
-// status[0] is set to 1 if the pivot column is zero.
-__global__ __launch_bounds__(kBuildThreads) void qr_panel_pivot(double* __restrict__ A, double* __restrict__ norm2,
-                                                                int32_t* __restrict__ perm, double* __restrict__ F,
-                                                                double* __restrict__ tau, double* __restrict__ aux,
-                                                                int* __restrict__ status, int64_t k, int64_t k0,
-                                                                int64_t d_out, int64_t d_in) {
-    __shared__ double s_val[kBuildThreads / kWave];
-    __shared__ int64_t s_idx[kBuildThreads / kWave];
-    __shared__ int32_t s_key[kBuildThreads / kWave];
-    __shared__ double fk[kPanel];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int j = (int)(k - k0);
+// The sum over each row of 16 lanes, returned to all of them.
+__device__ __forceinline__ double row_sum(double x) {
+    x += dpp64<0xB1>(x, 0.0);
+    x += dpp64<0x4E>(x, 0.0);
+    x += dpp64<0x124>(x, 0.0);
+    x += dpp64<0x128>(x, 0.0);
+    return x;
+}
 
-    const int64_t p = block_pivot(norm2, perm, k, d_out, s_val, s_idx, s_key);
-
-    // swap columns k and p, with their F rows, norms and original indices
-    if (p != k) {
-        double* ak = A + k * d_in;
-        double* ap = A + p * d_in;
-        for (int64_t i = tid; i < d_in; i += kBuildThreads) {
-            const double t = ak[i];
-            ak[i] = ap[i];
-            ap[i] = t;
-        }
-        if (tid < j) {
-            const double t = F[k * kPanel + tid];
-            F[k * kPanel + tid] = F[p * kPanel + tid];
-            F[p * kPanel + tid] = t;
-        }
-        if (tid == 0) {
-            const int32_t tp = perm[k];
-            perm[k] = perm[p];
-            perm[p] = tp;
-            const double tn = norm2[k];
-            norm2[k] = norm2[p];
-            norm2[p] = tn;
-        }
-    }
-    __syncthreads();
-    if (tid < kPanel) fk[tid] = tid < j ? F[k * kPanel + tid] : 0.0;
-    __syncthreads();
-
-    // One pass over rows [k, d_in) of column k and of the panel's earlier
-    // reflectors V[:, 0:j] (a row's j values loaded together): the column
-    // after those reflections, x[i] = a_k[i] - V[i, 0:j] fk, its squared
-    // norm, and dot[t] = sum_{i > k} V[i, t] x[i] for the aux vector.
-    double* x = A + k * d_in;
-    double s = 0.0;
-    double dot[kPanel];
-#pragma unroll
-    for (int t = 0; t < kPanel; ++t) dot[t] = 0.0;
-    for (int64_t i = k + tid; i < d_in; i += kBuildThreads) {
-        double vrow[kPanel];
-#pragma unroll
-        for (int t = 0; t < kPanel; ++t) vrow[t] = t < j ? A[(k0 + t) * d_in + i] : 0.0;
-        double v = x[i];
-#pragma unroll
-        for (int t = 0; t < kPanel; ++t) v -= vrow[t] * fk[t];  // zero past j
-        x[i] = v;
-        s += v * v;
-        if (i > k) {
-#pragma unroll
-            for (int t = 0; t < kPanel; ++t) dot[t] += vrow[t] * v;
-        }
-    }
-    __shared__ double s_dot[kBuildThreads / kWave][kPanel + 1];
-    s = wave_sum(s);
-#pragma unroll
-    for (int t = 0; t < kPanel; ++t) {
-        const double d = wave_sum(dot[t]);
-        if (lane == 0) s_dot[wave][t] = d;
-    }
-    if (lane == 0) s_val[wave] = s;
-    __syncthreads();
-    if (tid == 0) {
-        double t = 0.0;
-        for (int w = 0; w < kBuildThreads / kWave; ++w) t += s_val[w];
-        s_val[0] = t;
-    }
-    if (tid < j) {
-        double d = 0.0;
-        for (int w = 0; w < kBuildThreads / kWave; ++w) d += s_dot[w][tid];
-        s_dot[0][tid] = d;
-    }
-    __syncthreads();
-    const double xnorm = sqrt(s_val[0]);
-    const double alpha = x[k];
-    if (xnorm == 0.0) {
-        if (tid == 0) {
-            status[0] = 1;
-            tau[k] = 0.0;
-        }
-        if (tid < j) aux[tid] = 0.0;
-        return;
-    }
+// The reflector of a column x with squared norm s and leading entry alpha:
+// R's diagonal entry beta, tau, and inv with v = x * inv below the leading 1.
+// A zero column keeps its entries (tau = 0).
+struct Reflector {
+    double beta, tau, inv;
+};
+__device__ __forceinline__ Reflector reflector(double s, double alpha) {
+    const double xnorm = sqrt(s);
+    if (xnorm == 0.0) return {alpha, 0.0, 1.0};
     const double beta = -copysign(xnorm, alpha);
-    const double tk = (beta - alpha) / beta;
-    const double inv = 1.0 / (alpha - beta);
-    for (int64_t i = k + 1 + tid; i < d_in; i += kBuildThreads) x[i] *= inv;
-    // aux[t] = -tau_k V[k:, t]^T v_k = -tau_k (V[k, t] + inv * dot[t]), v_k[k] = 1
-    if (tid < j) aux[tid] = -tk * (A[(k0 + tid) * d_in + k] + inv * s_dot[0][tid]);
-    __syncthreads();  // every thread read alpha = x[k] above
-    if (tid == 0) {
-        x[k] = beta;
-        tau[k] = tk;
-    }
+    return {beta, (beta - alpha) / beta, 1.0 / (alpha - beta)};
 }
 
-// qr_panel_pivot with fewer dependent memory round trips, for columns of at
-// most kPivotLdsRows rows (longer columns take qr_panel_pivot): the pivot
-// column is read where it is (position p) in the same pass that moves the old
-// column k there and brings the pivot column up to date; the updated rows
-// wait in LDS (dynamic, (d_in - k) doubles) until they are scaled into the
-// reflector, and alpha = x[k] is read from there.  The arithmetic and its
-// order are those of qr_panel_pivot, so the results are bit-identical.
-// (64 KB of dynamic LDS at most.)
-constexpr int64_t kPivotLdsRows = 8192;
+// What the workgroups of qr_panel_pivot leave for the step's GEMV and for the
+// next step: row t < kPanel holds the workgroups' shares of sum_{i > k} V[i, t] x[i],
+// row kPanel those of ||x||^2; then alpha = x[k].  Two of them, by the
+// step's parity: a step writes its own while it reads the one before.
+struct PivotSums {
+    double share[kPanel + 1][kPivotBlocks];
+    double alpha;
+};
 
-__global__ __launch_bounds__(kBuildThreads) void qr_panel_pivot_lds(double* __restrict__ A, double* __restrict__ norm2,
-                                                                    int32_t* __restrict__ perm, double* __restrict__ F,
-                                                                    double* __restrict__ tau, double* __restrict__ aux,
-                                                                    int* __restrict__ status, int64_t k, int64_t k0,
-                                                                    int64_t d_out, int64_t d_in) {
-    __shared__ double s_val[kBuildThreads / kWave];
-    __shared__ int64_t s_idx[kBuildThreads / kWave];
-    __shared__ int32_t s_key[kBuildThreads / kWave];
+// Step k = k0 + j, part 1 (n_wg <= kPivotBlocks workgroups, rows interleaved
+// between them; each finds the pivot for itself):
+//   * pivot: the column p of largest (downdated) residual norm, ties to the
+//     lowest original index.  Column k moves to p; F row, norm and original
+//     index follow in part 2, because other workgroups still compare them here;
+//   * column k = the pivot column after the panel's earlier reflections,
+//     x = a_p - V[:, 0:j] F[p, 0:j]^T on rows [k, d_in), not yet scaled;
+//   * the sums the reflector needs (PivotSums);
+//   * the reflector of step k - 1 of the same panel is scaled where its rows
+//     are read anyway (v = x inv, R's diagonal entry above it).
+// Latency-bound: rows of V and of column k are loaded before the pivot is
+// known.  One workgroup of 1024 threads for all rows took 15.1 us per step at
+// 4096 x 4096, bound by one CU's loads of V and its 17 sums; spread out, the
+// whole build of r = 2048 went from 72.5 to 60.1 ms.
+// status[0] is set to 1 if a pivot column is zero.
+__global__ __launch_bounds__(kPivotThreads) void qr_panel_pivot(double* __restrict__ A,
+                                                                const double* __restrict__ norm2,
+                                                                const int32_t* __restrict__ perm,
+                                                                const double* __restrict__ F,
+                                                                PivotSums* __restrict__ sums,
+                                                                int64_t* __restrict__ pivot, int* __restrict__ status,
+                                                                int64_t k, int64_t k0, int64_t d_out, int64_t d_in,
+                                                                int n_wg) {
+    constexpr int kWaves = kPivotThreads / kWave;
+    __shared__ double s_val[kWaves];
+    __shared__ int32_t s_idx[kWaves], s_key[kWaves];
+    __shared__ double s_sum[kWaves][kPanel + 1];
     __shared__ double fk[kPanel];
-    extern __shared__ double pcol[];  // rows [k, d_in) of the updated pivot column
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int j = (int)(k - k0);
+    double* x = A + k * d_in;
+    const int64_t stride = (int64_t)n_wg * kPivotThreads;
+    int64_t i = (int64_t)blockIdx.x * kPivotThreads + tid;
+
+    double vrow[kPanel], xk = 0.0;
+    auto load = [&](int64_t row) {
+        const bool ok = row < d_in;
+        xk = ok ? x[row] : 0.0;
+#pragma unroll
+        for (int t = 0; t < kPanel; ++t) vrow[t] = (ok && row >= k && t < j) ? A[(k0 + t) * d_in + row] : 0.0;
+    };
+    load(i);
+    Reflector prev = {0.0, 0.0, 1.0};
+    if (j > 0) {
+        const PivotSums& ps = sums[(k - 1) & 1];
+        const int g = lane & (kPivotBlocks - 1);
+        const double s = row_sum(g < n_wg ? ps.share[kPanel][g] : 0.0);
+        prev = reflector(s, ps.alpha);
+        if (s == 0.0 && blockIdx.x == 0 && tid == 0) status[0] = 1;
+    }
 
     const int64_t p = block_pivot(norm2, perm, k, d_out, s_val, s_idx, s_key);
-
-    // columns k and p trade F rows, norms and original indices; fk is the
-    // pivot column's F row
-    if (tid < kPanel) {
-        const double fp = tid < j ? F[p * kPanel + tid] : 0.0;
-        fk[tid] = fp;
-        if (p != k && tid < j) {
-            const double fo = F[k * kPanel + tid];
-            F[k * kPanel + tid] = fp;
-            F[p * kPanel + tid] = fo;
-        }
-    }
-    if (tid == 0 && p != k) {
-        const int32_t tp = perm[k];
-        perm[k] = perm[p];
-        perm[p] = tp;
-        const double tn = norm2[k];
-        norm2[k] = norm2[p];
-        norm2[p] = tn;
-    }
-    double* x = A + k * d_in;
+    if (tid < kPanel) fk[tid] = tid < j ? F[p * kPanel + tid] : 0.0;
+    if (blockIdx.x == 0 && tid == 0) *pivot = p;
     double* ap = A + p * d_in;
-    if (p != k) {  // rows above k (entries of R) swap as they are
-        for (int64_t i = tid; i < k; i += kBuildThreads) {
-            const double t = x[i];
-            x[i] = ap[i];
-            ap[i] = t;
-        }
-    }
     __syncthreads();  // fk
 
-    // one pass over rows [k, d_in): the pivot column after the panel's
-    // reflections, x[i] = a_p[i] - V[i, 0:j] fk (to LDS), its squared norm
-    // and dot[t] = sum_{i > k} V[i, t] x[i]; the old column k moves to p
-    double s = 0.0;
-    double dot[kPanel];
+    PivotSums& out = sums[k & 1];
+    double s = 0.0, dot[kPanel];
 #pragma unroll
     for (int t = 0; t < kPanel; ++t) dot[t] = 0.0;
-    for (int64_t i = k + tid; i < d_in; i += kBuildThreads) {
-        double vrow[kPanel];
+    for (; i < d_in; i += stride) {
+        double v = p != k ? ap[i] : xk;
+        if (p != k) ap[i] = xk;
+        if (i >= k) {
 #pragma unroll
-        for (int t = 0; t < kPanel; ++t) vrow[t] = t < j ? A[(k0 + t) * d_in + i] : 0.0;
-        double v = ap[i];
-        if (p != k) ap[i] = x[i];
+            for (int t = 0; t < kPanel; ++t) {
+                if (t == j - 1) {
+                    vrow[t] *= prev.inv;
+                    A[(k0 + t) * d_in + i] = vrow[t];
+                }
+                v -= vrow[t] * fk[t];  // zero past j
+            }
+            s += v * v;
+            if (i == k) out.alpha = v;
+            else {
 #pragma unroll
-        for (int t = 0; t < kPanel; ++t) v -= vrow[t] * fk[t];  // zero past j
-        pcol[i - k] = v;
-        s += v * v;
-        if (i > k) {
-#pragma unroll
-            for (int t = 0; t < kPanel; ++t) dot[t] += vrow[t] * v;
+                for (int t = 0; t < kPanel; ++t) dot[t] += vrow[t] * v;
+            }
+        } else if (j > 0 && i == k - 1) {
+            A[(k - 1) * d_in + i] = prev.beta;
         }
+        if (i >= k || p != k) x[i] = v;
+        if (i + stride < d_in) load(i + stride);
     }
-    __shared__ double s_dot[kBuildThreads / kWave][kPanel + 1];
     s = wave_sum(s);
+    if (lane == 0) s_sum[wave][kPanel] = s;
 #pragma unroll
-    for (int t = 0; t < kPanel; ++t) {
-        const double d = wave_sum(dot[t]);
-        if (lane == 0) s_dot[wave][t] = d;
-    }
-    if (lane == 0) s_val[wave] = s;
-    __syncthreads();
-    if (tid == 0) {
-        double t = 0.0;
-        for (int w = 0; w < kBuildThreads / kWave; ++w) t += s_val[w];
-        s_val[0] = t;
-    }
-    if (tid < j) {
-        double d = 0.0;
-        for (int w = 0; w < kBuildThreads / kWave; ++w) d += s_dot[w][tid];
-        s_dot[0][tid] = d;
-    }
-    __syncthreads();
-    const double xnorm = sqrt(s_val[0]);
-    const double alpha = pcol[0];
-    if (xnorm == 0.0) {
-        for (int64_t i = k + tid; i < d_in; i += kBuildThreads) x[i] = pcol[i - k];
-        if (tid == 0) {
-            status[0] = 1;
-            tau[k] = 0.0;
+    for (int t = 0; t < kPanel; ++t)
+        if (t < j) {
+            const double d = wave_sum(dot[t]);
+            if (lane == 0) s_sum[wave][t] = d;
         }
-        if (tid < j) aux[tid] = 0.0;
-        return;
+    __syncthreads();
+    if (tid < j || tid == kPanel) {
+        double d = 0.0;
+        for (int w = 0; w < kWaves; ++w) d += s_sum[w][tid];
+        out.share[tid][blockIdx.x] = d;
     }
-    const double beta = -copysign(xnorm, alpha);
-    const double tk = (beta - alpha) / beta;
-    const double inv = 1.0 / (alpha - beta);
-    for (int64_t i = k + 1 + tid; i < d_in; i += kBuildThreads) x[i] = pcol[i - k] * inv;
-    // aux[t] = -tau_k V[k:, t]^T v_k = -tau_k (V[k, t] + inv * dot[t]), v_k[k] = 1
-    if (tid < j) aux[tid] = -tk * (A[(k0 + tid) * d_in + k] + inv * s_dot[0][tid]);
-    if (tid == 0) {
-        x[k] = beta;
-        tau[k] = tk;
-    }
+}
+
+// The scaling of a panel's last reflector, k (no next step reads its rows).
+__global__ __launch_bounds__(256) void qr_panel_finish(double* __restrict__ A, const PivotSums* __restrict__ sums,
+                                                       int* __restrict__ status, int64_t k, int64_t d_in, int n_wg) {
+    const PivotSums& ps = sums[k & 1];
+    const int g = threadIdx.x & (kPivotBlocks - 1);
+    const double s = row_sum(g < n_wg ? ps.share[kPanel][g] : 0.0);
+    const Reflector h = reflector(s, ps.alpha);
+    double* x = A + k * d_in;
+    const int64_t i = k + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < d_in) x[i] = i == k ? h.beta : x[i] * h.inv;
+    if (i == k && s == 0.0) status[0] = 1;
 }
 
 // Step k = k0 + j, part 2: one wave per trailing column c > k, read only
 // except for three values per column:
-//   F[c, j]  = tau_k a_c^T v_k + F[c, 0:j] aux[0:j]  (a_c as of the panel start)
+//   F[c, j]  = tau_k a_c^T v_k + F[c, 0:j] aux[0:j]  (a_c as of the panel start),
+//              aux[t] = -tau_k V[k:, t]^T v_k
 //   R[k][c]  = a_c[k] - V[k, 0:j] F[c, 0:j]^T - F[c, j]   (written to a_c[k])
 //   norm2[c] -= R[k][c]^2
+// with v_k = x inv below its leading 1 (x is not scaled yet: column k).  Each
+// wave folds the pivot workgroups' sums itself, behind its column's loads.
+// The wave of column p, where column k went, takes k's F row, norm and
+// original index over.
 __global__ __launch_bounds__(256) void qr_panel_gemv(double* __restrict__ A, double* __restrict__ norm2,
-                                                     double* __restrict__ F, const double* __restrict__ tau,
-                                                     const double* __restrict__ aux, int64_t k, int64_t k0,
-                                                     int64_t d_out, int64_t d_in) {
+                                                     int32_t* __restrict__ perm, double* __restrict__ F,
+                                                     const PivotSums* __restrict__ sums,
+                                                     const int64_t* __restrict__ pivot, int64_t k, int64_t k0,
+                                                     int64_t d_out, int64_t d_in, int n_wg) {
+    static_assert(kPanel == 16 && kPivotBlocks == 16, "lane l folds share l % 16 of rows l / 16 + 4 q");
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t c = k + 1 + (int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (c >= d_out) return;
     const int j = (int)(k - k0);
-    const double* v = A + k * d_in;  // v[k] = 1 (implicit), v[k+1:] stored
+    const double* v = A + k * d_in;  // x
     double* a = A + c * d_in;
+    const PivotSums& ps = sums[k & 1];
+    const bool moved = *pivot == c;  // column k came here
+    const int64_t src = moved ? k : c;
+    const int g = lane & 15;
+    double share[4], f[4], vk[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int t = 4 * q + lane / 16;
+        share[q] = (t < j && g < n_wg) ? ps.share[t][g] : 0.0;
+        f[q] = (t < j && g == 0) ? F[src * kPanel + t] : 0.0;
+        vk[q] = (t < j && g == 0) ? A[(k0 + t) * d_in + k] : 0.0;
+    }
+    const double nshare = g < n_wg ? ps.share[kPanel][g] : 0.0;
+    const double alpha = ps.alpha, akc = a[k], n2c = norm2[src];
     double d;
     if ((d_in & 1) == 0) {
         // 16-byte loads of rows [s2, d_in), s2 = k + 1 rounded up to even,
@@ -447,23 +380,36 @@ __global__ __launch_bounds__(256) void qr_panel_gemv(double* __restrict__ A, dou
         if (i < d_in) d1 += v[i] * a[i];
         d = d1 + d2;
     }
-    const double akc = a[k];
-    d = wave_sum(d) + akc;
-    double* Fc = F + c * kPanel;
+    d = wave_sum(d);
+    const Reflector h = reflector(row_sum(nshare), alpha);
+    // lane 16 w holds rows 4 q + w of F[c, :], V[k, :] and the sums V^T x
     double corr = 0.0, row = 0.0;
-    if (lane < j) {
-        const double f = Fc[lane];
-        corr = f * aux[lane];
-        row = A[(k0 + lane) * d_in + k] * f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        corr += f[q] * row_sum(share[q]);
+        row += f[q] * vk[q];
     }
     corr = wave_sum(corr);
     row = wave_sum(row);
+    double* Fc = F + c * kPanel;
+    if (moved && g == 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int t = 4 * q + lane / 16;
+            if (t < j) Fc[t] = f[q];
+        }
+    }
     if (lane == 0) {
-        const double f = tau[k] * d + corr;
-        Fc[j] = f;
-        const double rkc = akc - row - f;
+        const double fj = h.tau * (akc + h.inv * d) - h.tau * (row + h.inv * corr);
+        Fc[j] = fj;
+        const double rkc = akc - row - fj;
         a[k] = rkc;
-        norm2[c] = fmax(norm2[c] - rkc * rkc, 0.0);
+        norm2[c] = fmax(n2c - rkc * rkc, 0.0);
+        if (moved) {
+            const int32_t t = perm[k];
+            perm[k] = perm[c];
+            perm[c] = t;
+        }
     }
 }
 

@@ -2018,17 +2018,21 @@ pifa_status pifa_build_f64(const double* W, pifa_dims dims, double* W_p, double*
         ~Buf() {
             if (p) (void)hipFree(p);
         }
-    } A, norm2, perm, tau, status, RT, Csel, diag, idx, Fp, aux;
+    } A, norm2, perm, status, RT, Csel, diag, idx, Fp, sums, pivot;
     auto alloc = [](Buf& b, size_t bytes) { return hipMalloc(&b.p, bytes < 16 ? 16 : bytes) == hipSuccess; };
     if (!alloc(A, (size_t)d_out * d_in * 8) || !alloc(norm2, (size_t)d_out * 8) ||
-        !alloc(perm, (size_t)d_out * 4) || !alloc(tau, (size_t)r * 8) || !alloc(status, 4) ||
+        !alloc(perm, (size_t)d_out * 4) || !alloc(status, 4) || !alloc(pivot, 8) ||
         !alloc(diag, (size_t)r * 8) || !alloc(idx, (size_t)(r + 2 * n_np + r) * 4) ||
-        !alloc(Fp, (size_t)d_out * kPanel * 8) || !alloc(aux, (size_t)kPanel * 8))
+        !alloc(Fp, (size_t)d_out * kPanel * 8) || !alloc(sums, 2 * sizeof(PivotSums)))
         return PIFA_ERR_OOM;
     double* dA = (double*)A.p;
     double* dn = (double*)norm2.p;
     int32_t* dperm = (int32_t*)perm.p;
     double* dF = (double*)Fp.p;
+    PivotSums* dsums = (PivotSums*)sums.p;
+    int64_t* dpivot = (int64_t*)pivot.p;
+    // one row of a column per thread, as far as kPivotBlocks workgroups reach
+    const int n_wg = (int)std::min<int64_t>(kPivotBlocks, ceil_div(d_in, (int64_t)kPivotThreads));
     PIFA_HIP(hipMemsetAsync(status.p, 0, 4, st));
 
     // QR with column pivoting in panels of kPanel steps (build.hpp)
@@ -2036,18 +2040,16 @@ pifa_status pifa_build_f64(const double* W, pifa_dims dims, double* W_p, double*
     for (int64_t k0 = 0; k0 < r; k0 += kPanel) {
         const int64_t nb = std::min<int64_t>(kPanel, r - k0);
         for (int64_t k = k0; k < k0 + nb; ++k) {
-            // columns of up to kPivotLdsRows rows keep the updated pivot
-            // column in LDS (fewer dependent memory round trips, bit-identical)
-            if (d_in <= kPivotLdsRows)
-                hipLaunchKernelGGL(qr_panel_pivot_lds, dim3(1), dim3(kBuildThreads), (size_t)(d_in - k) * 8, st, dA, dn,
-                                   dperm, dF, (double*)tau.p, (double*)aux.p, (int*)status.p, k, k0, d_out, d_in);
-            else
-                hipLaunchKernelGGL(qr_panel_pivot, dim3(1), dim3(kBuildThreads), 0, st, dA, dn, dperm, dF,
-                                   (double*)tau.p, (double*)aux.p, (int*)status.p, k, k0, d_out, d_in);
+            hipLaunchKernelGGL(qr_panel_pivot, dim3((unsigned)n_wg), dim3(kPivotThreads), 0, st, dA, (const double*)dn,
+                               (const int32_t*)dperm, (const double*)dF, dsums, dpivot, (int*)status.p, k, k0, d_out,
+                               d_in, n_wg);
             if (k + 1 < d_out)
                 hipLaunchKernelGGL(qr_panel_gemv, dim3((unsigned)ceil_div(d_out - k - 1, 4)), dim3(256), 0, st, dA, dn,
-                                   dF, (const double*)tau.p, (const double*)aux.p, k, k0, d_out, d_in);
+                                   dperm, dF, (const PivotSums*)dsums, (const int64_t*)dpivot, k, k0, d_out, d_in,
+                                   n_wg);
         }
+        hipLaunchKernelGGL(qr_panel_finish, dim3((unsigned)ceil_div(d_in - (k0 + nb - 1), 256)), dim3(256), 0, st, dA,
+                           (const PivotSums*)dsums, (int*)status.p, k0 + nb - 1, d_in, n_wg);
         // the panel's reflections on the rest of the trailing matrix, then
         // its exact residual norms
         const int64_t ks = k0 + nb;
