@@ -173,6 +173,8 @@ __global__ __launch_bounds__(256) void gather_tile(const bf16* __restrict__ in, 
 // of a wave span a few hundred bytes (8 columns per lane, for 16-byte stores,
 // put 8 lanes on each bank: 25 us per 4096 x 4096 matrix where this takes 15), and a wave's
 // stores are 256 contiguous bytes.  Bound: memory.
+// The gridDim.y workgroups of the same rows share their output columns, 1024
+// at a time in turn (each reads the rows whole).
 // Dynamic LDS: R * round_up(d, 8) * 2 bytes.
 constexpr int kSplitRows = 4;  // R where they fit 64 KB
 
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(512) void split_columns(const bf16* __restrict__ in
     }
     __syncthreads();
     auto gather = [&](const int32_t* __restrict__ idx, int64_t n, bf16* __restrict__ out, int64_t ld) {
-        for (int64_t j = 2 * (int64_t)threadIdx.x; j < ld; j += 2 * 512) {
+        for (int64_t j = 2 * ((int64_t)blockIdx.y * 512 + threadIdx.x); j < ld; j += 2 * 512 * (int64_t)gridDim.y) {
             const int32_t c0 = idx[j < n ? j : n - 1], c1 = idx[j + 1 < n ? j + 1 : n - 1];
             for (int r = 0; r < nr; ++r) {
                 const uint32_t lo = j < n ? rows[r * pitch + c0] : 0, hi = j + 1 < n ? rows[r * pitch + c1] : 0;

@@ -323,6 +323,14 @@ void launch_dma(const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb, int
                            dim3((WM * WN + NP) * kWave), 0, st, A, lda, M, B, ldb, N, K, epi);
 }
 
+// Gradient products (fp32 outputs, K = the batch's rows) of at most this depth
+// are mostly their stores, which 128 x 128 register-staged tiles, two to a CU,
+// overlap with the next tile's loads and one 256 x 128 tile per CU does not:
+// backward of 4096 -> 11008, r = 2048, M = 64 86.2 -> 74.9 us, M = 400 140 ->
+// 125; 4096 -> 4096, r = 2048, M = 64 48.9 -> 46.8 us, M = 400 76.6 -> 75.3.
+// At 900 rows the direct loads are level, at 4096 10% ahead.
+constexpr int64_t kGradShortK = 512;
+
 template <typename T, bool BPACK, typename Epi, int KM = 0>
 hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb,
                        int64_t N, int64_t K, Epi epi, float* partials, hipStream_t st) {
@@ -337,7 +345,9 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
     // registers (512 x 2048 x 2048 on 64 x 64 tiles: 12.9 against 15.2 us).
     // K-major operands of unaligned callers' buffers (the backward's X) stay
     // with the register-staged loads too.
-    const bool direct = KM == 0 || (aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0);
+    constexpr bool kGrad = KM != 0 && std::is_same<Epi, RowsF32Epi>::value;
+    const bool direct =
+        KM == 0 || (aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 && !(kGrad && K <= kGradShortK));
     if (g.split.splits == 1 && direct && g.bm >= 128 && g.bn >= 128) {
         if (g.bm == 256 && g.bn == 256) {
             launch_dma<T, 256, 256, 2, 4, 2, 1, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
@@ -1413,13 +1423,20 @@ hipError_t launch_gather(const bf16* in, int64_t ld_in, int64_t M, const int32_t
 hipError_t launch_split(const bf16* in, int64_t d, int64_t M, const int32_t* ia, int64_t na, bf16* out_a, int64_t lda,
                         const int32_t* ib, int64_t nb, bf16* out_b, int64_t ldb, hipStream_t st) {
     constexpr int64_t kLds = 65536;
-    const int64_t row = round_up(d, (int64_t)8) * 2, rows = std::min<int64_t>(kSplitRows, kLds / row);
-    if (rows < 1) {
+    const int64_t row = round_up(d, (int64_t)8) * 2, fit = std::min<int64_t>(kSplitRows, kLds / row);
+    if (fit < 1) {
         hipError_t e = launch_gather(in, d, M, ia, na, out_a, lda, nullptr, 0, st);
         if (e == hipSuccess && out_b) e = launch_gather(in, d, M, ib, nb, out_b, ldb, nullptr, 0, st);
         return e;
     }
-    hipLaunchKernelGGL(split_columns, dim3((unsigned)ceil_div(M, rows)), dim3(512), (size_t)(rows * row), st, in, d, M,
+    // Few rows: fewer of them per workgroup, to keep two workgroups per CU, and
+    // below that several workgroups per row, for a shorter chain of index loads,
+    // LDS reads and stores in each (64 rows of 11008 columns: 16 workgroups of
+    // four rows made a backward pass of 53 us take 61).
+    const int64_t rows = std::max<int64_t>(1, std::min(fit, M / (2 * kCus))), wg = ceil_div(M, rows);
+    const int64_t cols = std::max(lda, out_b ? ldb : (int64_t)0);
+    const int64_t parts = rows > 1 ? 1 : std::max<int64_t>(1, std::min(8 * kCus / wg, ceil_div(cols, (int64_t)1024)));
+    hipLaunchKernelGGL(split_columns, dim3((unsigned)wg, (unsigned)parts), dim3(512), (size_t)(rows * row), st, in, d, M,
                        (int)rows, ia, na, out_a, lda, ib, nb, out_b, ldb);
     return hipGetLastError();
 }

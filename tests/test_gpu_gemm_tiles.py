@@ -93,10 +93,14 @@ def test_k_major_tile_edges(n, tokens, tile):
         assert np.all(np.abs(got.cpu().numpy() - 2 * (left.T @ b)) <= bound)
 
 
-@pytest.mark.parametrize("d_out,r,M", [(96, 33, 5), (4100, 2050, 3), (16392, 40, 3), (33000, 24, 2), (257, 257, 4)])
+@pytest.mark.parametrize("d_out,r,M", [(96, 33, 5), (4100, 2050, 3), (16392, 40, 3), (33000, 24, 2), (257, 257, 4),
+                                       # either side of the depth at which the gradient products' kernel
+                                       # changes (512 rows), and one and two rows per workgroup (1024)
+                                       (4100, 2050, 511), (4100, 2050, 513), (1500, 700, 1023), (1500, 700, 1025)])
 def test_backward_column_split(d_out, r, M):
     """The gather of a gradient's pivot and non-pivot columns: one and two rows
-    per workgroup, rows too long for LDS, odd row lengths, no non-pivot."""
+    per workgroup, rows shared by several, rows too long for LDS, odd row
+    lengths, no non-pivot."""
     torch = torch_mod()
     from paper_2501_19090_amd import inputs, pifa
     d_in = 264 if r <= 264 else 2056
