@@ -1,7 +1,8 @@
 """The pivot steps of the GPU build at the edges of their split: rows just
-below, at and past one workgroup's 512, past all sixteen workgroups' 8192;
-panels of one step, one short of, at and past 16; square, wide and tall;
-every row a pivot; and equal rows, whose ties go to the lowest index."""
+below, at and past one workgroup's 512 and all sixteen workgroups' 8192;
+columns that come to fit LDS within a build; panels of one step, one short
+of, at and past 16; square, wide and tall; every row a pivot; and equal rows,
+whose ties go to the lowest index."""
 import numpy as np
 import pytest
 
@@ -34,7 +35,7 @@ def _check(W, r):
 
 @pytest.mark.parametrize("d_out,d_in,r", [
     (70, 511, 1), (70, 512, 15), (70, 513, 16), (4200, 40, 17), (33, 1025, 33),
-    (17, 16, 16), (1, 8, 1), (50, 8192, 20), (50, 16385, 18),
+    (17, 16, 16), (1, 8, 1), (50, 8192, 20), (50, 16385, 18), (30, 8200, 24),
 ])
 def test_step_edges(d_out, d_in, r):
     U, V = inputs.lowrank_factors(d_out, d_in, r, seed=3 * d_out + r)
