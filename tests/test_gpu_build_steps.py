@@ -1,8 +1,7 @@
 """The pivot steps of the GPU build at the edges of their split: rows just
 below, at and past one workgroup's 512 and all sixteen workgroups' 8192;
-columns that come to fit LDS within a build; panels of one step, one short
-of, at and past 16; square, wide and tall; every row a pivot; and equal rows,
-whose ties go to the lowest index."""
+panels of one step, one short of, at and past 16; square, wide and tall;
+every row a pivot; and equal rows, whose ties go to the lowest index."""
 import numpy as np
 import pytest
 
