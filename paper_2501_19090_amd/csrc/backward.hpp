@@ -239,31 +239,41 @@ struct GradPivotEpi {
         const float g = bf16_bits_to_f32(g16[(m < M ? m : 0) * r_pad + (c.ok ? c.n : 0)]);
         return (c.ok && m < M) ? g : 0.f;
     }
+    // A run of W columns starts at a multiple of 8 and goes in pieces of 8,
+    // each wholly inside or wholly past the r_pad columns: where W does not
+    // divide r_pad's unit of 64 (24, on the 256 x 192 tile) the last run of a
+    // row is cut.
     template <int W>
     __device__ __forceinline__ void init_run(int64_t m, int64_t n, float (&v)[W]) const {
         static_assert(W % 8 == 0, "16-byte loads");
-        const u32x4* src = reinterpret_cast<const u32x4*>(gpi + (m < M ? m : 0) * r_pad + (n + W <= r_pad ? n : 0));
+        const bf16* row = gpi + (m < M ? m : 0) * r_pad;
         u32x4 w[W / 8];
 #pragma unroll
-        for (int x = 0; x < W / 8; ++x) w[x] = src[x];
-        const uint32_t keep = n + W <= r_pad ? 0xFFFFFFFFu : 0u;
+        for (int x = 0; x < W / 8; ++x)
+            w[x] = *reinterpret_cast<const u32x4*>(row + (n + 8 * x < r_pad ? n + 8 * x : 0));
 #pragma unroll
         for (int x = 0; x < W / 2; ++x) {
-            const uint32_t u = w[x / 4][x % 4] & keep;
+            const uint32_t u = n + 8 * (x / 4) < r_pad ? w[x / 4][x % 4] : 0u;
             v[2 * x] = bf16_bits_to_f32((uint16_t)u);
             v[2 * x + 1] = bf16_bits_to_f32((uint16_t)(u >> 16));
         }
     }
     template <int W>
     __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
-        if (m >= M || n + W > r_pad) return;
-        f32x4* d = reinterpret_cast<f32x4*>(gp + m * r_pad + n);
-        uint16_t h[W];
+        static_assert(W % 8 == 0, "pieces of 8 columns");
+        if (m >= M) return;
+        float* d = gp + m * r_pad + n;
+        uint16_t* b = reinterpret_cast<uint16_t*>(gpb) + m * r_pad + n;
 #pragma unroll
-        for (int x = 0; x < W / 4; ++x) d[x] = f32x4{v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]};
+        for (int x = 0; x < W; x += 8) {
+            if (n + x >= r_pad) return;
+            uint16_t h[8];
 #pragma unroll
-        for (int x = 0; x < W; ++x) h[x] = f32_to_bf16_bits(v[x]);
-        store_run16<W>(reinterpret_cast<uint16_t*>(gpb) + m * r_pad + n, h);
+            for (int e = 0; e < 8; ++e) h[e] = f32_to_bf16_bits(v[x + e]);
+            reinterpret_cast<f32x4*>(d + x)[0] = f32x4{v[x], v[x + 1], v[x + 2], v[x + 3]};
+            reinterpret_cast<f32x4*>(d + x)[1] = f32x4{v[x + 4], v[x + 5], v[x + 6], v[x + 7]};
+            store_run16<8>(b + x, h);
+        }
     }
     __device__ __forceinline__ void store(int64_t m, const Col& c, float v) const {
         if (m >= M || !c.ok) return;

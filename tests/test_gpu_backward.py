@@ -91,6 +91,53 @@ def test_backward_full_size_sampled():
         lay.close()
 
 
+@pytest.mark.parametrize("M,r,tile", [
+    (4096, 4041, (256, 256)),   # r_pad = 4096
+    (4096, 2560, (256, 192)),   # r_pad = 2560: the last 64 of 192 columns
+    (4090, 2750, (256, 192)),   # r_pad = 2752, the same; the last two are padding
+    (4096, 2810, (256, 192)),   # r_pad = 2816: the last 128 of 192 columns, six of them padding
+    (4096, 2304, (256, 192)),   # r_pad = 2304: whole tiles
+    (4001, 2000, (256, 128)),
+    (2041, 1990, (128, 128)),
+])
+def test_backward_pivot_gradient_tiles(M, r, tile):
+    """G_p on every output tile that it can take, at ranks whose last tile is
+    cut at different columns, with large values of an earlier, longer call
+    still in the workspace.  The last pivot columns are compared on their own
+    too: a few wrong columns are little of the whole gradient."""
+    from paper_2501_19090_amd import pifa
+    torch = torch_mod()
+    n_np = 44
+    d_in, d_out = (r + 7) // 8 * 8, r + n_np
+    assert pifa.pifa_gemm_plan(M, -(-r // 64) * 64, -(-n_np // 8) * 8)[:2] == tile
+    rng = np.random.default_rng(r)
+    piv, npiv = inputs.random_partition(d_out, r, 3)
+    lay = DeviceLayer(piv, npiv, rng.standard_normal((r, d_in)) * r ** -0.5,
+                      rng.standard_normal((n_np, r)) * r ** -0.5, "bf16")
+    try:
+        x_dev, _ = activations(M + 256, d_in, 5, "bf16")
+        g_dev, _ = activations(M + 256, d_out, 6, "bf16")
+        _grads(lay, x_dev, g_dev * 4096, M + 256)
+        x_dev, x64 = activations(M, d_in, 7, "bf16")
+        g_dev, g64 = activations(M, d_out, 8, "bf16")
+        dX, dWp, dC = _grads(lay, x_dev, g_dev, M)
+        # dX row by row, dW_p and dC by pivot slots (as in the full-size test)
+        rows = sample_rows(M, k=254)
+        rX, _, _ = oracle.pifa_backward(x64[rows], g64[rows], lay.piv, lay.npiv, lay.Wp, lay.C)
+        assert rel_fro(from_dev(dX)[rows], rX) <= TOL
+        S = np.unique(np.concatenate([np.arange(0, r, 97), np.arange(r - 32, r)]))
+        Gs = np.concatenate([g64[:, lay.piv[S]], g64[:, lay.npiv]], axis=1)
+        piv_s = np.arange(S.size, dtype=np.int32)
+        npiv_s = np.arange(S.size, S.size + n_np, dtype=np.int32)
+        _, rW, rC = oracle.pifa_backward(x64, Gs, piv_s, npiv_s, lay.Wp[S], lay.C[:, S])
+        for part in (slice(None), slice(-8, None), slice(-32, None)):
+            assert rel_fro(from_dev(dWp)[S][part], rW[part]) <= TOL
+            assert rel_fro(from_dev(dC)[:, S][:, part], rC[:, part]) <= TOL
+        assert torch.isfinite(dX).all() and torch.isfinite(dWp).all() and torch.isfinite(dC).all()
+    finally:
+        lay.close()
+
+
 def test_backward_deterministic_and_optional_outputs():
     from paper_2501_19090_amd import pifa
     torch = torch_mod()
