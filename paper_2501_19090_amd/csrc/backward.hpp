@@ -212,13 +212,13 @@ __global__ __launch_bounds__(512) void split_columns(const bf16* __restrict__ in
 // Epilogue of G_p = G[:, I^c] C (+ G[:, I]): acc(m, n) for n < r_pad.
 //   * the accumulator starts from gpi[m * r_pad + n] = G[m, piv[n]] (zeros at
 //     n >= r), the gathered pivot columns (init);
-//   * writes G_p in fp32 to gp[m * r_pad + n] (padding columns n >= r get
-//     zeros), for the row-wise fp16 conversion;
-//   * writes bf16(G_p) to gpb[m * r_pad + n] (zeros at n >= r): the K-major
-//     A operand of dW_p = G_p^T X.
-// The padding columns need no mask: C^T's padding rows and their starting
-// values are zero.  gpi, gp and gpb have 16-byte aligned rows (r_pad is a
-// multiple of 64).
+//   * writes G_p in fp32 to gp[m * r_pad + n], for the row-wise fp16
+//     conversion;
+//   * writes bf16(G_p) to gpb[m * r_pad + n]: the K-major A operand of
+//     dW_p = G_p^T X.
+// The padding columns are not masked here: C^T's padding rows and their
+// starting values are zero, and no reader takes more than r columns.  gpi, gp
+// and gpb have 16-byte aligned rows (r_pad is a multiple of 64).
 struct GradPivotEpi {
     static constexpr bool kRowsPlusStaged = true;
     const bf16* gpi;
@@ -292,18 +292,26 @@ struct GradPivotEpi {
     }
 };
 
-// Row m of gp (n = r_pad fp32 values, n % 4 == 0) -> fp16 out[m][:] times
-// 2^s_m with the row's largest |value| in [2^14, 2^15) (s_m = 0 for a zero
-// row), and inv[m] = 2^-s_m.  One workgroup of 256 threads per row.
-__global__ __launch_bounds__(256) void rows_to_f16(const float* __restrict__ gp, int64_t n, f16* __restrict__ out,
-                                                   float* __restrict__ inv) {
+// Row m of gp (n = r_pad fp32 values, n % 4 == 0, of which r are G_p's and
+// the rest count as zero) -> fp16 out[m][:] times 2^s_m with the row's largest
+// |value| in [2^14, 2^15) (s_m = 0 for a zero row), and inv[m] = 2^-s_m.
+// One workgroup of 256 threads per row.
+__global__ __launch_bounds__(256) void rows_to_f16(const float* __restrict__ gp, int64_t r, int64_t n,
+                                                   f16* __restrict__ out, float* __restrict__ inv) {
     __shared__ float red[256 / kWave];
     const int64_t m = blockIdx.x;
     const f32x4* row = reinterpret_cast<const f32x4*>(gp + m * n);
     const int64_t nq = n / 4;
+    // a padding column is NaN where the gradient's row holds an infinity (the
+    // product's zero weights times it): as a zero it adds nothing to dX
+    auto load = [&](int64_t q) {
+        f32x4 v = row[q];
+        for (int e = 0; e < 4; ++e) v[e] = 4 * q + e < r ? v[e] : 0.f;
+        return v;
+    };
     float mx = 0.f;
     for (int64_t q = threadIdx.x; q < nq; q += 256) {
-        const f32x4 v = row[q];
+        const f32x4 v = load(q);
         mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
     }
     for (int off = kWave / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
@@ -319,7 +327,7 @@ __global__ __launch_bounds__(256) void rows_to_f16(const float* __restrict__ gp,
     }
     const float sc = ldexpf(1.f, s);
     for (int64_t q = threadIdx.x; q < nq; q += 256) {
-        const f32x4 v = row[q];
+        const f32x4 v = load(q);
         f16 h[4] = {(f16)(v[0] * sc), (f16)(v[1] * sc), (f16)(v[2] * sc), (f16)(v[3] * sc)};
         *reinterpret_cast<uint64_t*>(out + m * n + 4 * q) = __builtin_bit_cast(uint64_t, h);
     }

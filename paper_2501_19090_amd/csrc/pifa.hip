@@ -1499,7 +1499,7 @@ pifa_status pifa_layer_backward(pifa_handle h, const void* X, const void* Y, con
     if (dX) {  // dX = (G_p 2^s_m in fp16) (W_p^T 2^cw in fp16)^T 2^-(s_m + cw)
         {
             TimedLaunch timed(kSiteBwdRows, st);
-            hipLaunchKernelGGL(rows_to_f16, dim3((unsigned)M), dim3(256), 0, st, gp32, r_pad, gp16, inv);
+            hipLaunchKernelGGL(rows_to_f16, dim3((unsigned)M), dim3(256), 0, st, gp32, r, r_pad, gp16, inv);
             if (hipGetLastError() != hipSuccess) return PIFA_ERR_HIP;
         }
         e = launch_gemm<f16, true>(kSiteBwdDx, gp16, r_pad, M, (const f16*)h->bwd_wpt, 0, d_in, r_pad,

@@ -138,6 +138,27 @@ def test_backward_pivot_gradient_tiles(M, r, tile):
         lay.close()
 
 
+@pytest.mark.parametrize("M,r", [(3, 1), (300, 40), (4096, 1000)])
+def test_backward_infinite_gradient(M, r):
+    """An infinity in a non-pivot gradient reaches dX with its sign: the rank's
+    padding adds nothing to the row."""
+    n_np, d_in = 3, (r + 7) // 8 * 8
+    piv, npiv = inputs.random_partition(r + n_np, r, 3)
+    lay = DeviceLayer(piv, npiv, np.ones((r, d_in)), np.ones((n_np, r)), "bf16")
+    try:
+        x_dev, _ = activations(M, d_in, 7, "bf16")
+        g_dev, g64 = activations(M, r + n_np, 8, "bf16")
+        inf = np.arange(1, M, 97)
+        g_dev[inf, int(npiv[1])] = float("inf")
+        dX = from_dev(_grads(lay, x_dev, g_dev, M)[0])
+        assert np.all(dX[inf] == np.inf)
+        rows = np.setdiff1d(np.arange(M), inf)
+        Gp = g64[rows][:, piv] + g64[rows][:, npiv].sum(1, keepdims=True)
+        assert rel_fro(dX[rows], np.repeat(Gp.sum(1, keepdims=True), d_in, 1)) <= TOL
+    finally:
+        lay.close()
+
+
 def test_backward_deterministic_and_optional_outputs():
     from paper_2501_19090_amd import pifa
     torch = torch_mod()
