@@ -215,10 +215,11 @@ struct RowsF32Epi {
     __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
         if (m >= M || n >= N) return;
         float* dst = out + m * ldo + n;
-        if (n + W <= N && (ldo & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+        if (n + W <= N) {  // 16-byte stores, which global memory takes at 4-byte alignment
+            typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
 #pragma unroll
             for (int x = 0; x < W / 4; ++x)
-                reinterpret_cast<f32x4*>(dst)[x] = f32x4{v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]};
+                reinterpret_cast<f32x4_a4*>(dst)[x] = f32x4{v[4 * x], v[4 * x + 1], v[4 * x + 2], v[4 * x + 3]};
         } else {
 #pragma unroll
             for (int x = 0; x < W; ++x)
