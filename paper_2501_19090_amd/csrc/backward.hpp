@@ -167,46 +167,95 @@ __global__ __launch_bounds__(256) void gather_tile(const bf16* __restrict__ in, 
 // Rows of in (M x d, row stride d) split by column sets: out_a[m][j] =
 // in[m][ia[j]] for j < na (zeros up to lda) and, if out_b, out_b[m][j] =
 // in[m][ib[j]] for j < nb (zeros up to ldb); lda and ldb are even and the
-// outputs 4-byte aligned.  One workgroup takes R rows: they are read once,
-// whole lines at a time, into LDS, and gathered from there, a lane taking two
-// neighbouring columns of every row: with sorted indices the 2-byte LDS reads
-// of a wave span a few hundred bytes (8 columns per lane, for 16-byte stores,
-// put 8 lanes on each bank: 25 us per 4096 x 4096 matrix where this takes 15), and a wave's
-// stores are 256 contiguous bytes.  Bound: memory.
-// The gridDim.y workgroups of the same rows share their output columns, 1024
-// at a time in turn (each reads the rows whole).
-// Dynamic LDS: R * round_up(d, 8) * 2 bytes.
-constexpr int kSplitRows = 4;  // R where they fit 64 KB
+// outputs 4-byte aligned.  Both kernels below give a lane two neighbouring
+// columns of several rows, so that a wave's stores are 256 contiguous bytes.
+struct ColumnSplit {
+    const bf16* in;
+    int64_t d, M;
+    const int32_t* ia;
+    int64_t na;
+    bf16* out_a;
+    int64_t lda;
+    const int32_t* ib;
+    int64_t nb;
+    bf16* out_b;
+    int64_t ldb;
 
-__global__ __launch_bounds__(512) void split_columns(const bf16* __restrict__ in, int64_t d, int64_t M, int R,
-                                                     const int32_t* __restrict__ ia, int64_t na,
-                                                     bf16* __restrict__ out_a, int64_t lda,
-                                                     const int32_t* __restrict__ ib, int64_t nb,
-                                                     bf16* __restrict__ out_b, int64_t ldb) {
+    int64_t pairs() const { return (lda + (out_b ? ldb : 0)) / 2; }
+
+    // pair p of the output columns: a's, then b's
+    struct Pair {
+        int32_t c0, c1;  // source columns, -1 for a zero
+        uint16_t* out;
+        int64_t ld;
+    };
+    __device__ __forceinline__ Pair pair(int64_t p) const {
+        const bool b = 2 * p >= lda;
+        const int32_t* idx = b ? ib : ia;
+        const int64_t n = b ? nb : na, j = b ? 2 * p - lda : 2 * p;
+        const int32_t c0 = idx[j < n ? j : n - 1], c1 = idx[j + 1 < n ? j + 1 : n - 1];
+        return Pair{j < n ? c0 : -1, j + 1 < n ? c1 : -1, reinterpret_cast<uint16_t*>(b ? out_b : out_a) + j,
+                    b ? ldb : lda};
+    }
+};
+
+// A workgroup reads R rows once, whole lines at a time, into LDS and gathers
+// from there: with sorted indices the 2-byte LDS reads of a wave span a few
+// hundred bytes (8 columns per lane, for 16-byte stores, put 8 lanes on each
+// bank).  The rows are one span of memory, read in 16-byte units from the
+// boundary below its start, whatever its alignment.  Bound: memory.
+// Dynamic LDS: R rows and, unless every row starts on a 16-byte boundary, 16
+// bytes more.
+constexpr int kSplitRows = 4;  // R, and rows per lane of the direct form
+
+__global__ __launch_bounds__(512) void split_columns(ColumnSplit s, int R) {
     extern __shared__ __attribute__((aligned(16))) uint16_t rows[];
     const int64_t m0 = (int64_t)blockIdx.x * R;
-    const int nr = (int)((M - m0) < R ? (M - m0) : R);
-    const int64_t pitch = round_up(d, (int64_t)8);
-    const uint16_t* src = reinterpret_cast<const uint16_t*>(in) + m0 * d;
-    if ((d & 7) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {
-        for (int64_t q = threadIdx.x; q < nr * d / 8; q += 512)
-            reinterpret_cast<u32x4*>(rows)[q] = reinterpret_cast<const u32x4*>(src)[q];
-    } else {
-        for (int r = 0; r < nr; ++r)
-            for (int64_t j = threadIdx.x; j < d; j += 512) rows[r * pitch + j] = src[r * d + j];
+    const int nr = (int)((s.M - m0) < R ? (s.M - m0) : R);
+    const uint16_t* src = reinterpret_cast<const uint16_t*>(s.in) + m0 * s.d;
+    const int shift = (int)((reinterpret_cast<uintptr_t>(src) & 15) / 2);  // LDS position of the first value
+    const int64_t n = nr * s.d, units = ceil_div(shift + n, (int64_t)8);
+    if ((m0 > 0 || shift == 0) && 8 * units - shift <= (s.M - m0) * s.d) {
+        const u32x4* span = reinterpret_cast<const u32x4*>(src - shift);
+        for (int64_t q = threadIdx.x; q < units; q += 512) reinterpret_cast<u32x4*>(rows)[q] = span[q];
+    } else {  // the matrix starts or ends inside a unit
+        for (int64_t e = threadIdx.x; e < n; e += 512) rows[shift + e] = src[e];
     }
     __syncthreads();
-    auto gather = [&](const int32_t* __restrict__ idx, int64_t n, bf16* __restrict__ out, int64_t ld) {
-        for (int64_t j = 2 * ((int64_t)blockIdx.y * 512 + threadIdx.x); j < ld; j += 2 * 512 * (int64_t)gridDim.y) {
-            const int32_t c0 = idx[j < n ? j : n - 1], c1 = idx[j + 1 < n ? j + 1 : n - 1];
+    auto gather = [&](const int32_t* __restrict__ idx, int64_t ni, bf16* __restrict__ out, int64_t ld) {
+        for (int64_t j = 2 * threadIdx.x; j < ld; j += 2 * 512) {
+            const int32_t c0 = idx[j < ni ? j : ni - 1], c1 = idx[j + 1 < ni ? j + 1 : ni - 1];
             for (int r = 0; r < nr; ++r) {
-                const uint32_t lo = j < n ? rows[r * pitch + c0] : 0, hi = j + 1 < n ? rows[r * pitch + c1] : 0;
-                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + (m0 + r) * ld + j) = lo | (hi << 16);
+                const uint16_t* row = rows + shift + r * s.d;
+                const uint32_t x = j < ni ? row[c0] : 0, y = j + 1 < ni ? row[c1] : 0;
+                *reinterpret_cast<uint32_t*>(reinterpret_cast<uint16_t*>(out) + (m0 + r) * ld + j) = x | (y << 16);
             }
         }
     };
-    gather(ia, na, out_a, lda);
-    if (out_b) gather(ib, nb, out_b, ldb);
+    gather(s.ia, s.na, s.out_a, s.lda);
+    if (s.out_b) gather(s.ib, s.nb, s.out_b, s.ldb);
+}
+
+// Straight from memory, kSplitRows rows per lane with their loads in flight
+// together: no barrier and no pass through LDS, but a line is asked for once
+// per 2-byte value.  Grid: (ceil(M / kSplitRows), ceil(pairs / 256)).
+__global__ __launch_bounds__(256) void split_columns_direct(ColumnSplit s) {
+    const int64_t p = (int64_t)blockIdx.y * 256 + threadIdx.x, m0 = (int64_t)blockIdx.x * kSplitRows;
+    if (p >= (s.lda + (s.out_b ? s.ldb : 0)) / 2) return;
+    const ColumnSplit::Pair c = s.pair(p);
+    const uint16_t* src = reinterpret_cast<const uint16_t*>(s.in);
+    uint32_t x[kSplitRows], y[kSplitRows];
+#pragma unroll
+    for (int r = 0; r < kSplitRows; ++r) {  // unconditional, from valid addresses
+        const uint16_t* row = src + (m0 + r < s.M ? m0 + r : s.M - 1) * s.d;
+        x[r] = row[c.c0 >= 0 ? c.c0 : 0];
+        y[r] = row[c.c1 >= 0 ? c.c1 : 0];
+    }
+#pragma unroll
+    for (int r = 0; r < kSplitRows; ++r)
+        if (m0 + r < s.M)
+            *reinterpret_cast<uint32_t*>(c.out + (m0 + r) * c.ld) =
+                (c.c0 >= 0 ? x[r] : 0u) | (c.c1 >= 0 ? y[r] << 16 : 0u);
 }
 
 // Epilogue of G_p = G[:, I^c] C (+ G[:, I]): acc(m, n) for n < r_pad.

@@ -1419,25 +1419,22 @@ hipError_t launch_gather(const bf16* in, int64_t ld_in, int64_t M, const int32_t
     return hipGetLastError();
 }
 
-// split_columns (see backward.hpp); rows too long for LDS are gathered from memory.
-hipError_t launch_split(const bf16* in, int64_t d, int64_t M, const int32_t* ia, int64_t na, bf16* out_a, int64_t lda,
-                        const int32_t* ib, int64_t nb, bf16* out_b, int64_t ldb, hipStream_t st) {
-    constexpr int64_t kLds = 65536;
-    const int64_t row = round_up(d, (int64_t)8) * 2, fit = std::min<int64_t>(kSplitRows, kLds / row);
-    if (fit < 1) {
-        hipError_t e = launch_gather(in, d, M, ia, na, out_a, lda, nullptr, 0, st);
-        if (e == hipSuccess && out_b) e = launch_gather(in, d, M, ib, nb, out_b, ldb, nullptr, 0, st);
-        return e;
-    }
-    // Few rows: fewer of them per workgroup, to keep two workgroups per CU, and
-    // below that several workgroups per row, for a shorter chain of index loads,
-    // LDS reads and stores in each (64 rows of 11008 columns: 16 workgroups of
-    // four rows made a backward pass of 53 us take 61).
-    const int64_t rows = std::max<int64_t>(1, std::min(fit, M / (2 * kCus))), wg = ceil_div(M, rows);
-    const int64_t cols = std::max(lda, out_b ? ldb : (int64_t)0);
-    const int64_t parts = rows > 1 ? 1 : std::max<int64_t>(1, std::min(8 * kCus / wg, ceil_div(cols, (int64_t)1024)));
-    hipLaunchKernelGGL(split_columns, dim3((unsigned)wg, (unsigned)parts), dim3(512), (size_t)(rows * row), st, in, d, M,
-                       (int)rows, ia, na, out_a, lda, ib, nb, out_b, ldb);
+// The gathers of a gradient's columns (see backward.hpp).  Through LDS where
+// there are many rows and a large matrix: M x d, us for both gathers of a pass,
+// LDS / direct: 4096 x 4096 26 / 29, 8192 x 8192 115 / 132; 8192 x 2048 28 /
+// 29; but 2048 x 8192 40 / 37, 4096 x 2048 18 / 17, 1024 x 11008 34 / 30.
+constexpr int64_t kSplitLdsMinM = 4096, kSplitLdsMinElems = 1 << 24;
+
+hipError_t launch_split(const ColumnSplit& s, hipStream_t st) {
+    const int64_t row = s.d * 2, pad = aligned16(s.in) && s.d % 8 == 0 ? 0 : 16;  // the span's start in its 16-byte unit
+    const int64_t R = std::min<int64_t>(kSplitRows, (65536 - pad) / row);
+    if (R > 0 && s.M >= kSplitLdsMinM && s.M * s.d >= kSplitLdsMinElems)
+        hipLaunchKernelGGL(split_columns, dim3((unsigned)ceil_div(s.M, R)), dim3(512),
+                           (size_t)round_up(R * row + pad, (int64_t)16), st, s, (int)R);
+    else
+        hipLaunchKernelGGL(split_columns_direct,
+                           dim3((unsigned)ceil_div(s.M, (int64_t)kSplitRows), (unsigned)ceil_div(s.pairs(), (int64_t)256)),
+                           dim3(256), 0, st, s);
     return hipGetLastError();
 }
 
@@ -1485,12 +1482,10 @@ pifa_status pifa_layer_backward(pifa_handle h, const void* X, const void* Y, con
     {  // the gathered columns G[:, I^c], G[:, I] and Y[:, I] as rows
         TimedLaunch timed(kSiteBwdData, st);
         bf16* gpi = (bf16*)gp16;
-        if ((e = launch_split(G, d_out, M, h->piv, r, gpi, r_pad, h->npiv, n_np, n_np > 0 ? gic : nullptr, ldc, st)) !=
-            hipSuccess)
-            return PIFA_ERR_HIP;
-        if (n_np > 0 && dC &&
-            (e = launch_split((const bf16*)Y, d_out, M, h->piv, r, ypr, ldy, nullptr, 0, nullptr, 0, st)) != hipSuccess)
-            return PIFA_ERR_HIP;
+        const ColumnSplit of_g{G, d_out, M, h->piv, r, gpi, r_pad, h->npiv, n_np, n_np > 0 ? gic : nullptr, ldc};
+        if ((e = launch_split(of_g, st)) != hipSuccess) return PIFA_ERR_HIP;
+        const ColumnSplit of_y{(const bf16*)Y, d_out, M, h->piv, r, ypr, ldy, nullptr, 0, nullptr, 0};
+        if (n_np > 0 && dC && (e = launch_split(of_y, st)) != hipSuccess) return PIFA_ERR_HIP;
     }
     // G_p = G[:, I^c] C + G[:, I] in fp32, and bf16(G_p)
     e = launch_gemm<bf16, true>(kSiteBwdGp, gic, ldc, M, (const bf16*)h->bwd_ct, 0, r_pad, ldc,

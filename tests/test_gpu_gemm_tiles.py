@@ -95,12 +95,15 @@ def test_k_major_tile_edges(n, tokens, tile):
 
 @pytest.mark.parametrize("d_out,r,M", [(96, 33, 5), (4100, 2050, 3), (16392, 40, 3), (33000, 24, 2), (257, 257, 4),
                                        # either side of the depth at which the gradient products' kernel
-                                       # changes (512 rows), and one and two rows per workgroup (1024)
-                                       (4100, 2050, 511), (4100, 2050, 513), (1500, 700, 1023), (1500, 700, 1025)])
-def test_backward_column_split(d_out, r, M):
-    """The gather of a gradient's pivot and non-pivot columns: one and two rows
-    per workgroup, rows shared by several, rows too long for LDS, odd row
-    lengths, no non-pivot."""
+                                       # changes (512 rows)
+                                       (4100, 2050, 511), (4100, 2050, 513), (1500, 700, 1023), (1500, 700, 1025),
+                                       # through LDS: whole 16-byte units, and rows that start inside one
+                                       (4104, 40, 4097), (4101, 40, 4098)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_backward_column_split(d_out, r, M, offset):
+    """The gather of a gradient's pivot and non-pivot columns: few and many
+    rows, long rows, odd row lengths, no non-pivot; offset: gradients and
+    outputs that start inside a 16-byte unit."""
     torch = torch_mod()
     from paper_2501_19090_amd import inputs, pifa
     d_in = 264 if r <= 264 else 2056
@@ -116,7 +119,13 @@ def test_backward_column_split(d_out, r, M):
     dX = torch.empty((M, d_in), dtype=torch.bfloat16, device="cuda:0")
     dWp = torch.empty((r, d_in), dtype=torch.float32, device="cuda:0")
     dC = torch.empty((d_out - r, r), dtype=torch.float32, device="cuda:0")
-    pifa.pifa_layer_backward(lay.handle, X.to("cuda:0"), Yb.to("cuda:0"), G.to("cuda:0"), dX, dWp, dC)
+
+    def at_offset(t):
+        buf = torch.full((t.numel() + offset,), float("nan"), dtype=t.dtype, device="cuda:0")
+        buf[offset:] = t.flatten().to("cuda:0")
+        return buf[offset:].view(t.shape)
+
+    pifa.pifa_layer_backward(lay.handle, X.to("cuda:0"), at_offset(Yb), at_offset(G), dX, dWp, dC)
     torch.cuda.synchronize()
     lay.close()
     Gp = Gd[:, piv] + Gd[:, npiv] @ Cd
