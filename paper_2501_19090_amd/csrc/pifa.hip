@@ -243,22 +243,24 @@ size_t split_bytes(int64_t M, int64_t N, int64_t K) {
     return g.split.splits > 1 ? (size_t)(g.split.splits * M * N) * 4 : 0;
 }
 
-// Prefill tile configurations and a cost model to pick one: time ~ rounds
-// of concurrently resident tiles x tile area x tiles sharing a CU / relative
-// efficiency.  Measured per-FLOP rates of whole rounds relative to 256 x 128
-// (TFLOP/s of a 4096 x 4096 x 8192 product 1230, 256 x 256 tiles 1345; 4096 x
-// 3072 x 4096 on 256 x 192 tiles 1148 against 969 on two rounds of 256 x 128
-// and 1083 on 192 of the 256 CUs with 256 x 256): about 1.12, 1.08 and, with
-// half the LDS reuse and one workgroup per CU, 0.8 for 128 x 128.
+// Prefill tile configurations and a cost model to pick one: time ~ rounds of
+// concurrently resident tiles x their area / relative efficiency.  Measured
+// per-FLOP rates of whole rounds relative to 256 x 128 (TFLOP/s of a 4096 x
+// 4096 x 8192 product 1230, 256 x 256 tiles 1345; 4096 x 3072 x 4096 on 256 x
+// 192 tiles 1148 against 969 on two rounds of 256 x 128 and 1083 on 192 of the
+// 256 CUs with 256 x 256): about 1.12, 1.08 and, with half the LDS reuse and
+// one workgroup per CU, 0.8 for 128 x 128.  More 128 x 128 tiles than CUs run
+// two to a CU (launch_gemm): 462 to 495 of them, 2048 deep, in 40 us where one
+// round of 256 x 128 takes 32 to 34: the same 0.8.
 TileCfg pick_tile(int64_t M, int64_t N, int wide) {
-    struct C { int64_t bm, bn, per_cu; double eff; };
-    const C cfg[4] = {{256, 256, 1, 1.12}, {256, 192, 1, 1.08}, {256, 128, 1, 1.0}, {128, 128, 1, 0.8}};
+    struct C { int64_t bm, bn; double eff; };
+    const C cfg[4] = {{256, 256, 1.12}, {256, 192, 1.08}, {256, 128, 1.0}, {128, 128, 0.8}};
     int best = 3;
     double best_t = 1e300;
     for (int i = 0; i < 4; ++i) {
         if ((i < 2 && wide == kWideNone) || (i == 1 && wide == kWideSquare)) continue;
         const int64_t tiles = ceil_div(M, cfg[i].bm) * ceil_div(N, cfg[i].bn);
-        const double t = (double)ceil_div(tiles, kCus * cfg[i].per_cu) * cfg[i].bm * cfg[i].bn / cfg[i].eff;
+        const double t = (double)ceil_div(tiles, kCus) * cfg[i].bm * cfg[i].bn / cfg[i].eff;
         if (t < best_t * 0.999) {
             best_t = t;
             best = i;
@@ -348,6 +350,7 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
     constexpr bool kGrad = KM != 0 && std::is_same<Epi, RowsF32Epi>::value;
     const bool direct =
         KM == 0 || (aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 && !(kGrad && K <= kGradShortK));
+    const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128);
     if (g.split.splits == 1 && direct && g.bm >= 128 && g.bn >= 128) {
         if (g.bm == 256 && g.bn == 256) {
             launch_dma<T, 256, 256, 2, 4, 2, 1, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
@@ -355,6 +358,12 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
             if constexpr (KM == 0) launch_dma<T, 256, 192, 4, 2, 2, 1, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
         } else if (g.bm == 256) {
             launch_dma<T, 256, 128, 4, 2, 3, 2, 4, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
+        } else if (t128 > kCus) {
+            // two stages, two workgroups per CU: one's stores and first loads
+            // run beside the other's products (four stages and one workgroup,
+            // 1290 x 5488 x 256 14.0 us against 11.0; 1080 x 6861 x 1024 31.6
+            // against 27.4; 1855 x 4115 x 2048 53.4 against 39.6)
+            launch_dma<T, 128, 128, 2, 4, 2, 2, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
         } else {
             launch_dma<T, 128, 128, 2, 4, 4, 2, 4, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
         }

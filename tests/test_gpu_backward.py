@@ -99,6 +99,7 @@ def test_backward_full_size_sampled():
     (4096, 2304, (256, 192)),   # r_pad = 2304: whole tiles
     (4001, 2000, (256, 128)),
     (2041, 1990, (128, 128)),
+    (1855, 4100, (128, 128)),   # 495 tiles, two to a CU
 ])
 def test_backward_pivot_gradient_tiles(M, r, tile):
     """G_p on every output tile that it can take, at ranks whose last tile is

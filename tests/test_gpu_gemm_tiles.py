@@ -35,6 +35,10 @@ def _bf16(shape, seed):
     (4033, 2040, 8, (256, 128)),    # a single 8-deep K chunk
     (2041, 2040, 200, (128, 128)),
     (1921, 2047, 328, (128, 128)),
+    # more 128 x 128 tiles than CUs, two to a CU
+    (1855, 4120, 136, (128, 128)),
+    (1855, 4115, 328, (128, 128)),
+    (1855, 4115, 776, (128, 128)),
 ])
 @pytest.mark.parametrize("packed", [True, False])
 def test_tile_edges(M, N, K, tile, packed):
@@ -98,7 +102,9 @@ def test_k_major_tile_edges(n, tokens, tile):
                                        # changes (512 rows)
                                        (4100, 2050, 511), (4100, 2050, 513), (1500, 700, 1023), (1500, 700, 1025),
                                        # through LDS: whole 16-byte units, and rows that start inside one
-                                       (4104, 40, 4097), (4101, 40, 4098)])
+                                       (4104, 40, 4097), (4101, 40, 4098),
+                                       # dC of 128 x 128 tiles two to a CU
+                                       (5970, 4115, 520)])
 @pytest.mark.parametrize("offset", [0, 1])
 def test_backward_column_split(d_out, r, M, offset):
     """The gather of a gradient's pivot and non-pivot columns: few and many
@@ -106,7 +112,7 @@ def test_backward_column_split(d_out, r, M, offset):
     outputs that start inside a 16-byte unit."""
     torch = torch_mod()
     from paper_2501_19090_amd import inputs, pifa
-    d_in = 264 if r <= 264 else 2056
+    d_in = 264 if r <= 264 else max(2056, (r + 7) // 8 * 8)
     piv, npiv = inputs.random_partition(d_out, r, 9)
     Wp, C = _bf16((r, d_in), 5), _bf16((d_out - r, r), 6)
     X, G = _bf16((M, d_in), 7), _bf16((M, d_out), 8)
