@@ -325,6 +325,24 @@ void launch_dma(const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb, int
                            dim3((WM * WN + NP) * kWave), 0, st, A, lda, M, B, ldb, N, K, epi);
 }
 
+// Products of at most this depth whose epilogue scatters bf16 columns run
+// through registers: their stores are most of the time, and leave sooner from
+// the 32 x 32 accumulators of two workgroups per CU than row by row through
+// LDS.  Direct / register-staged, us, odd rows of outputs: 256 x 192 tiles
+// (3653 x 6174 x 64) 28.1 / 24.3, (4482 x 2076 x 256) 18.0 / 16.5, (3640 x 2798
+// x 768) 26.2 / 26.1; 256 x 256 tiles (5932 x 4973 x 128) 34.7 / 32.0, (3863 x
+// 7155 x 768) 60.3 / 61.1; up to 256 tiles of 128 x 128 (2885 x 1140 x 256) 9.4
+// / 8.8, (4877 x 613 x 768) 12.9 / 12.5, (703 x 4878 x 2048) 23.0 / 23.6; up to
+// 512 of them, two to a CU either way (1895 x 2878 x 512) 15.7 / 15.6, (1855 x
+// 4115 x 2048) 39.6 / 46.8.  256 x 128 tiles are faster direct at any depth.
+// 256 x 192 tiles whose rows of A are not whole 128-byte lines go through
+// registers at any depth: a row's piece of a K tile then lies in two lines,
+// and with two LDS stages nothing is left to wait with (2050 x 4175 x 3824 84.5
+// / 77.6, 2217 x 3825 x 5416 124 / 103, 882 x 9455 x 2584 55.8 / 55.8, 5710 x
+// 1902 x 1848 48.1 / 48.8; lines, 2720 x 3232 x 2048 46.7 / 46.8, 2759 x 3590 x
+// 4096 80.6 / 84.4).
+constexpr int64_t kScatterShortK = 768;
+
 // Gradient products (fp32 outputs, K = the batch's rows) of at most this depth
 // are mostly their stores, which 128 x 128 register-staged tiles, two to a CU,
 // overlap with the next tile's loads and one 256 x 128 tile per CU does not:
@@ -346,11 +364,17 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
     // waves per workgroup have no loads to wait behind, are faster through
     // registers (512 x 2048 x 2048 on 64 x 64 tiles: 12.9 against 15.2 us).
     // K-major operands of unaligned callers' buffers (the backward's X) stay
-    // with the register-staged loads too.
+    // with the register-staged loads too, and so do shallow products that are
+    // mostly their stores.
     constexpr bool kGrad = KM != 0 && std::is_same<Epi, RowsF32Epi>::value;
-    const bool direct =
-        KM == 0 || (aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 && !(kGrad && K <= kGradShortK));
+    constexpr bool kScatter = KM == 0 && (DualEpiT<Epi>::value || ScatterRowsT<Epi>::value);
     const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128);
+    const bool staged = kScatter && !(g.bm == 256 && g.bn == 128) &&
+                        (K <= kScatterShortK || (g.bn == 192 && lda % 64 != 0));
+    const bool direct = KM == 0
+                            ? !staged
+                            : aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 &&
+                                  !(kGrad && K <= kGradShortK);
     if (g.split.splits == 1 && direct && g.bm >= 128 && g.bn >= 128) {
         if (g.bm == 256 && g.bn == 256) {
             launch_dma<T, 256, 256, 2, 4, 2, 1, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
@@ -368,16 +392,30 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
             launch_dma<T, 128, 128, 2, 4, 4, 2, 4, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);
         }
     } else if (g.split.splits == 1) {
-        if (g.bm == 64)
+        if (g.bm == 64) {
             hipLaunchKernelGGL((gemm_nt_mfma<T, 64, 64, kGemmBK, 2, 2, BPACK, 2, Epi, KM>), grid, dim3(4 * kWave), 0,
                                st, A, lda, M, B, ldb, N, K, K, epi);
-        else if (g.bn == 64)
+        } else if (g.bn == 64) {
             hipLaunchKernelGGL((gemm_nt_mfma<T, 128, 64, kGemmBK, 4, 2, BPACK, 2, Epi, KM>), grid, dim3(8 * kWave), 0,
                                st, A, lda, M, B, ldb, N, K, K, epi);
-        else if constexpr (KM != 0)
-            hipLaunchKernelGGL((gemm_nt_mfma<T, 128, 128, kGemmBK, 4, 2, BPACK, 2, Epi, KM>),
-                               dim3((unsigned)(ceil_div(M, 128) * ceil_div(N, 128))), dim3(8 * kWave), 0, st, A, lda, M,
-                               B, ldb, N, K, K, epi);
+        } else if (kScatter && g.bm == 256) {
+            if constexpr (kScatter) {
+                auto wide = [&](const auto& e) {
+                    using E = std::decay_t<decltype(e)>;
+                    if (g.bn == 256)
+                        hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 256, kGemmBK, 2, 4, BPACK, 1, E, KM>), grid,
+                                           dim3(8 * kWave), 0, st, A, lda, M, B, ldb, N, K, K, e);
+                    else
+                        hipLaunchKernelGGL((gemm_nt_mfma<T, 256, 192, kGemmBK, 4, 2, BPACK, 2, E, KM>), grid,
+                                           dim3(8 * kWave), 0, st, A, lda, M, B, ldb, N, K, K, e);
+                };
+                if constexpr (DualEpiT<Epi>::value) wide(epi.elementwise());
+                else wide(epi);
+            }
+        } else if constexpr (KM != 0 || kScatter) {
+            hipLaunchKernelGGL((gemm_nt_mfma<T, 128, 128, kGemmBK, 4, 2, BPACK, 2, Epi, KM>), dim3((unsigned)t128),
+                               dim3(8 * kWave), 0, st, A, lda, M, B, ldb, N, K, K, epi);
+        }
     } else {
         SplitEpi se{partials, M, N};
         const dim3 sgrid(grid.x, (unsigned)g.split.splits);
