@@ -344,11 +344,13 @@ void launch_dma(const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb, int
 constexpr int64_t kScatterShortK = 768;
 
 // Gradient products (fp32 outputs, K = the batch's rows) of at most this depth
-// are mostly their stores, which 128 x 128 register-staged tiles, two to a CU,
-// overlap with the next tile's loads and one 256 x 128 tile per CU does not:
-// backward of 4096 -> 11008, r = 2048, M = 64 86.2 -> 74.9 us, M = 400 140 ->
-// 125; 4096 -> 4096, r = 2048, M = 64 48.9 -> 46.8 us, M = 400 76.6 -> 75.3.
-// At 900 rows the direct loads are level, at 4096 10% ahead.
+// are mostly their stores too, which 128 x 128 register-staged tiles, two to a
+// CU, overlap with the next tile's loads: 1105 x 4208 x 128 12.2 us (256 x 128
+// direct 13.2), 1020 x 6432 x 512 18.8 (20.3), 2780 x 6656 x 512 35.1 (48.6);
+// 1380 x 4224 x 777 23.4 (24.0), 1123 x 4488 x 4096 78 (64.5).  Up to 256 such
+// tiles the direct form is level.  A product that 256 x 256 tiles finish in
+// one round keeps them (3075 x 4720 x 200 22.0 us against 25.6; 5405 x 2780 x
+// 512 27.9 against 35.7).
 constexpr int64_t kGradShortK = 512;
 
 template <typename T, bool BPACK, typename Epi, int KM = 0>
@@ -374,7 +376,7 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
     const bool direct = KM == 0
                             ? !staged
                             : aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 &&
-                                  !(kGrad && K <= kGradShortK);
+                                  !(kGrad && K <= kGradShortK && !(g.bn == 256 && (int64_t)grid.x <= kCus));
     if (g.split.splits == 1 && direct && g.bm >= 128 && g.bn >= 128) {
         if (g.bm == 256 && g.bn == 256) {
             launch_dma<T, 256, 256, 2, 4, 2, 1, 0, AM, BMD>(A, lda, M, B, ldb, N, K, epi, st);

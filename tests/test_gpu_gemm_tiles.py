@@ -110,8 +110,8 @@ def test_k_major_tile_edges(n, tokens, tile):
                                        (4100, 2050, 511), (4100, 2050, 513), (1500, 700, 1023), (1500, 700, 1025),
                                        # through LDS: whole 16-byte units, and rows that start inside one
                                        (4104, 40, 4097), (4101, 40, 4098),
-                                       # dC of 128 x 128 tiles two to a CU
-                                       (5970, 4115, 520)])
+                                       # dC of 128 x 128 tiles two to a CU, and shallow on one round of 256 x 256
+                                       (5970, 4115, 520), (7075, 4000, 200)])
 @pytest.mark.parametrize("offset", [0, 1])
 def test_backward_column_split(d_out, r, M, offset):
     """The gather of a gradient's pivot and non-pivot columns: few and many
