@@ -259,8 +259,12 @@ __global__ __launch_bounds__(256) void split_columns_direct(ColumnSplit s) {
 }
 
 // Epilogue of G_p = G[:, I^c] C (+ G[:, I]): acc(m, n) for n < r_pad.
-//   * the accumulator starts from gpi[m * r_pad + n] = G[m, piv[n]] (zeros at
-//     n >= r), the gathered pivot columns (init);
+//   * adds gpi[m * r_pad + n] = G[m, piv[n]] (zeros at n >= r), the gathered
+//     pivot columns: the register-staged tiles and the K-split reduction start
+//     from it (init), the direct tiles add it to the finished sums (Old).
+//     Loaded ahead of the loop it left the 256 x 256 and 256 x 192 tiles 32 to
+//     126 registers short, which they spilled around every K tile: 4096 x 3648
+//     x 496 71 us, 4096 x 2880 x 8144 269, so 48 and 214;
 //   * writes G_p in fp32 to gp[m * r_pad + n], for the row-wise fp16
 //     conversion;
 //   * writes bf16(G_p) to gpb[m * r_pad + n]: the K-major A operand of
@@ -293,34 +297,37 @@ struct GradPivotEpi {
     // divide r_pad's unit of 64 (24, on the 256 x 192 tile) the last run of a
     // row is cut.
     template <int W>
-    __device__ __forceinline__ void init_run(int64_t m, int64_t n, float (&v)[W]) const {
-        static_assert(W % 8 == 0, "16-byte loads");
+    struct Old {
+        u32x4 g[W / 8];
+    };
+    template <int W>
+    __device__ __forceinline__ Old<W> old(int64_t m, int64_t n) const {
+        static_assert(W % 8 == 0, "pieces of 8 columns");
         const bf16* row = gpi + (m < M ? m : 0) * r_pad;
-        u32x4 w[W / 8];
+        Old<W> o;
 #pragma unroll
         for (int x = 0; x < W / 8; ++x)
-            w[x] = *reinterpret_cast<const u32x4*>(row + (n + 8 * x < r_pad ? n + 8 * x : 0));
-#pragma unroll
-        for (int x = 0; x < W / 2; ++x) {
-            const uint32_t u = n + 8 * (x / 4) < r_pad ? w[x / 4][x % 4] : 0u;
-            v[2 * x] = bf16_bits_to_f32((uint16_t)u);
-            v[2 * x + 1] = bf16_bits_to_f32((uint16_t)(u >> 16));
-        }
+            o.g[x] = *reinterpret_cast<const u32x4*>(row + (n + 8 * x < r_pad ? n + 8 * x : 0));
+        return o;
     }
     template <int W>
-    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W]) const {
-        static_assert(W % 8 == 0, "pieces of 8 columns");
+    __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W], const Old<W>& o) const {
         if (m >= M) return;
         float* d = gp + m * r_pad + n;
         uint16_t* b = reinterpret_cast<uint16_t*>(gpb) + m * r_pad + n;
 #pragma unroll
         for (int x = 0; x < W; x += 8) {
             if (n + x >= r_pad) return;
+            float s[8];
             uint16_t h[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = f32_to_bf16_bits(v[x + e]);
-            reinterpret_cast<f32x4*>(d + x)[0] = f32x4{v[x], v[x + 1], v[x + 2], v[x + 3]};
-            reinterpret_cast<f32x4*>(d + x)[1] = f32x4{v[x + 4], v[x + 5], v[x + 6], v[x + 7]};
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t u = o.g[x / 8][e / 2];
+                s[e] = v[x + e] + bf16_bits_to_f32((uint16_t)(e % 2 ? u >> 16 : u));
+                h[e] = f32_to_bf16_bits(s[e]);
+            }
+            reinterpret_cast<f32x4*>(d + x)[0] = f32x4{s[0], s[1], s[2], s[3]};
+            reinterpret_cast<f32x4*>(d + x)[1] = f32x4{s[4], s[5], s[6], s[7]};
             store_run16<8>(b + x, h);
         }
     }

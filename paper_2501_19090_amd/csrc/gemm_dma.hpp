@@ -349,16 +349,6 @@ __device__ __forceinline__ void gemm_dma_tile(const T* __restrict__ A, int64_t l
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if constexpr (InitEpi<Epi>::value) {
-            static_assert(kDealt, "starting values of a dealt product");
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                float v[W];
-                epi.template init_run<W>(run_row(i), run_col(0), v);
-#pragma unroll
-                for (int x = 0; x < W; ++x) acc[i][x / 4][x & 3] = v[x];
-            }
-        }
     }
 
     const int grp = (wave % NW) >= NW / 2 ? 1 : 0;
