@@ -314,20 +314,22 @@ struct AccF64Epi {
     // A run's old values are loaded ahead of the run before it (Old): added in
     // place run by run, every run waited a memory round trip for its own (a
     // 4096 x 4096 x 2048 product 113 us, 106 so; the lower tiles 95, 90).
+    // 16-byte accesses, which global memory takes at 8-byte alignment, so rows
+    // of any length take them.
+    typedef double f64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
     template <int W>
     struct Old {
         double v[W];
     };
     template <int W>
     __device__ __forceinline__ Old<W> old(int64_t m, int64_t n) const {
-        typedef double f64x2 __attribute__((ext_vector_type(2)));
         Old<W> o;
         // unconditional, from a valid address, where the run is whole
-        const bool whole = m < M && n + W <= N && (ld & 1) == 0;
-        const f64x2* src = reinterpret_cast<const f64x2*>(out + (whole ? m * ld + n : 0));
+        const bool whole = m < M && n + W <= N;
+        const f64x2_a8* src = reinterpret_cast<const f64x2_a8*>(out + (whole ? m * ld + n : 0));
 #pragma unroll
         for (int x = 0; x < W / 2; ++x) {
-            const f64x2 s = src[x];
+            const f64x2_a8 s = src[x];
             o.v[2 * x] = s[0];
             o.v[2 * x + 1] = s[1];
         }
@@ -337,12 +339,11 @@ struct AccF64Epi {
     __device__ __forceinline__ void run(int64_t m, int64_t n, const float (&v)[W], const Old<W>& o) const {
         if (m >= M || n >= N) return;
         double* dst = out + m * ld + n;
-        if (n + W <= N && (ld & 1) == 0) {  // 16-byte rows (out is the handle's allocation)
-            typedef double f64x2 __attribute__((ext_vector_type(2)));
+        if (n + W <= N) {
 #pragma unroll
             for (int x = 0; x < W / 2; ++x)
-                reinterpret_cast<f64x2*>(dst)[x] =
-                    f64x2{o.v[2 * x] + (double)v[2 * x], o.v[2 * x + 1] + (double)v[2 * x + 1]};
+                reinterpret_cast<f64x2_a8*>(dst)[x] =
+                    f64x2_a8{o.v[2 * x] + (double)v[2 * x], o.v[2 * x + 1] + (double)v[2 * x + 1]};
         } else {
 #pragma unroll
             for (int x = 0; x < W; ++x)

@@ -83,10 +83,27 @@ def test_tile_edges(M, N, K, tile, packed):
     (2400, 64, (256, 128)),
 ])
 def test_k_major_tile_edges(n, tokens, tile):
-    torch = torch_mod()
     from paper_2501_19090_amd import pifa
     got_tile = pifa.pifa_gemm_plan(n, n, tokens)
     assert got_tile == tile + (1,) or (tile == (256, 128) and got_tile[:2] == (256, 192))
+    _check_sums(n, tokens)
+
+
+@pytest.mark.parametrize("n,tokens,tile", [
+    (3, 600, (64, 64)), (2001, 72, (128, 128)), (2052, 64, (256, 128)), (2399, 77, (256, 128)),
+    (3333, 130, (256, 192)), (4001, 72, (256, 256)),
+])
+def test_calibration_sums_of_unaligned_rows(n, tokens, tile):
+    """Activation rows that are not whole 16-byte units, and sums with rows of
+    any length: the products run on transposed copies."""
+    from paper_2501_19090_amd import pifa
+    assert pifa.pifa_gemm_plan(n, n, -(-tokens // 8) * 8)[:2] == tile
+    _check_sums(n, tokens)
+
+
+def _check_sums(n, tokens):
+    torch = torch_mod()
+    from paper_2501_19090_amd import pifa
     xo, xu = _bf16((tokens, n), 3), _bf16((tokens, n), 4)
     h = pifa.pifa_calib_create(n)
     S = torch.empty((n, n), dtype=torch.float64, device="cuda:0")
