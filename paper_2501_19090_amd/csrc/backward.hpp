@@ -215,7 +215,7 @@ __global__ __launch_bounds__(512) void split_columns(ColumnSplit s, int R) {
     const uint16_t* src = reinterpret_cast<const uint16_t*>(s.in) + m0 * s.d;
     const int shift = (int)((reinterpret_cast<uintptr_t>(src) & 15) / 2);  // LDS position of the first value
     const int64_t n = nr * s.d, units = ceil_div(shift + n, (int64_t)8);
-    if ((m0 > 0 || shift == 0) && 8 * units - shift <= (s.M - m0) * s.d) {
+    if (m0 * s.d >= shift && 8 * units - shift <= (s.M - m0) * s.d) {
         const u32x4* span = reinterpret_cast<const u32x4*>(src - shift);
         for (int64_t q = threadIdx.x; q < units; q += 512) reinterpret_cast<u32x4*>(rows)[q] = span[q];
     } else {  // the matrix starts or ends inside a unit

@@ -323,8 +323,9 @@ struct AccF64Epi {
     };
     template <int W>
     __device__ __forceinline__ Old<W> old(int64_t m, int64_t n) const {
-        Old<W> o;
-        // unconditional, from a valid address, where the run is whole
+        Old<W> o{};
+        if (M * ld < W) return o;  // no run of these sums is whole (the same for every lane)
+        // unconditional, from a valid address, where the run is not whole
         const bool whole = m < M && n + W <= N;
         const f64x2_a8* src = reinterpret_cast<const f64x2_a8*>(out + (whole ? m * ld + n : 0));
 #pragma unroll
