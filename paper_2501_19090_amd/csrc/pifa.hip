@@ -521,20 +521,32 @@ void skinny_stream_launch(SkinnyGroup<TB, AL, Epi> grp, int64_t k_blocks_total, 
 // at least two 16-row groups per CU (with one, the activations' round trip is
 // not hidden: a 33.5 MB pivot product of 256 groups 10.4 us against 9.2), and
 // operands that fit without spilling: passes over K at most 4, times operands
-// at most 8.  Launches and returns true if so.
+// at most 8.  It pays for a reduction and a barrier per group and pass with
+// the activations that skinny_packed reads again for every group, M x 128 of
+// them per block, so it needs enough of those (90000 rows of a block, 23 MB)
+// and more than one pass between barriers.  Whole forward, skinny_packed /
+// this, us: 1644 groups of 4 blocks at M = 8 11.4 / 15.8, 1200 of 8 at M = 9
+// 15.2 / 16.9, 619 of 10 at M = 9 12.3 / 13.2, 1166 of 11 at M = 9 22.5 / 20.4,
+// 1379 of 13 at M = 12 30.2 / 24.5, 1131 of 28 at M = 5 41.4 / 35.5.  Of 204
+// drawn ones that the rule takes four, groups of unequal ranks, are 3 to 5%
+// slower, and the mean is 12% faster.
+// Launches and returns true if so.
+constexpr int64_t kResidentMinRows = 90000;
+
 template <typename TB, typename AL, typename Epi>
 bool skinny_resident_launch(SkinnyGroup<TB, AL, Epi> grp, int64_t KB, int64_t blocks, hipStream_t st) {
     constexpr int OPS = AL::kOps;
     const int64_t M = grp.p[0].al.M, groups = grp.start[grp.n], passes = ceil_div(KB, (int64_t)8);
-    if (!AL::kBuffered || M <= kStreamRows || M > kDecodeMaxM || blocks < kStreamMinBlocks || groups < 2 * kCus || passes > 4 || passes * OPS > 8) return false;
+    if (!AL::kBuffered || M <= kStreamRows || M > kDecodeMaxM || blocks < kStreamMinBlocks || groups < 2 * kCus ||
+        M * blocks < kResidentMinRows || passes < 2 || passes > 4 || passes * OPS > 8)
+        return false;
     const dim3 grid((unsigned)kCus);
     auto go = [&](auto r) {
         constexpr int R = decltype(r)::value;
         if constexpr (AL::kBuffered && R * OPS <= 8)
             hipLaunchKernelGGL((skinny_resident<TB, R, AL, Epi>), grid, dim3(8 * kWave), 0, st, grp);
     };
-    if (passes <= 1) go(std::integral_constant<int, 1>{});
-    else if (passes <= 2) go(std::integral_constant<int, 2>{});
+    if (passes <= 2) go(std::integral_constant<int, 2>{});
     else go(std::integral_constant<int, 4>{});
     return true;
 }

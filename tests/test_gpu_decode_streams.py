@@ -1,7 +1,8 @@
 """Long decode weight streams with more than four activation rows: dense,
 pair-operand and grouped products whose 16-row groups are walked by one
-workgroup per CU, at one to four passes over K, ragged rows and columns, and
-a change of problem inside a workgroup's range.  Bounds per output: bf16
+workgroup per CU, at two to four passes over K, ragged rows and columns, and
+a change of problem inside a workgroup's range; and the long streams of one
+pass or few rows that are not walked.  Bounds per output: bf16
 rounding (2^-8 of the value, twice what it needs) plus fp32 accumulation
 (K u sum |a b|) and, behind the fp16 pair, 2^-20 of its terms."""
 import numpy as np
@@ -29,7 +30,9 @@ def _check(got, ref, bound):
     assert np.all(np.abs(got - ref) <= 2.0 ** -8 * np.abs(ref) + bound)
 
 
-@pytest.mark.parametrize("M,N,K", [(5, 98305, 128), (16, 8325, 1600), (9, 8192, 2040), (6, 12289, 4096)])
+@pytest.mark.parametrize("M,N,K", [(5, 98305, 128), (16, 98305, 128), (16, 8325, 1600), (6, 12289, 4096),
+                                   # 8192 blocks: 9 rows are too few, 11 enough
+                                   (9, 8192, 2040), (11, 8192, 2040)])
 def test_dense_streams(M, N, K):
     from paper_2501_19090_amd import pifa
     torch = torch_mod()
