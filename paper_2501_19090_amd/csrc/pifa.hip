@@ -332,7 +332,7 @@ void launch_dma(const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb, int
 // (3653 x 6174 x 64) 28.1 / 24.3, (4482 x 2076 x 256) 18.0 / 16.5, (3640 x 2798
 // x 768) 26.2 / 26.1; 256 x 256 tiles (5932 x 4973 x 128) 34.7 / 32.0, (3863 x
 // 7155 x 768) 60.3 / 61.1; up to 256 tiles of 128 x 128 (2885 x 1140 x 256) 9.4
-// / 8.8, (4877 x 613 x 768) 12.9 / 12.5, (703 x 4878 x 2048) 23.0 / 23.6; up to
+// / 8.8, (5417 x 467 x 1024) 14.4 / 14.1, (703 x 4878 x 2048) 23.0 / 23.6; up to
 // 512 of them, two to a CU either way (1895 x 2878 x 512) 15.7 / 15.6, (1855 x
 // 4115 x 2048) 39.6 / 46.8.  256 x 128 tiles are faster direct at any depth.
 // 256 x 192 tiles whose rows of A are not whole 128-byte lines go through
@@ -340,8 +340,13 @@ void launch_dma(const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb, int
 // and with two LDS stages nothing is left to wait with (2050 x 4175 x 3824 84.5
 // / 77.6, 2217 x 3825 x 5416 124 / 103, 882 x 9455 x 2584 55.8 / 55.8, 5710 x
 // 1902 x 1848 48.1 / 48.8; lines, 2720 x 3232 x 2048 46.7 / 46.8, 2759 x 3590 x
-// 4096 80.6 / 84.4).
-constexpr int64_t kScatterShortK = 768;
+// 4096 80.6 / 84.4).  Up to 256 tiles of 128 x 128 the same rows cost the
+// direct form only where few tile rows have them read by many workgroups at a
+// time (461 x 5235 x 5416 55.8 / 51.7, 260 x 9804 x 2584 29.6 / 28.1, 1106 x
+// 3131 x 3824 38.3 / 39.6; 2301 x 1518 x 2584 27.4 / 28.4, 7647 x 443 x 3824
+// 36.2 / 38.7; lines, 703 x 4878 x 2048 23.0 / 23.6).
+constexpr int64_t kScatterShortK = 768, kScatterShortK128 = 1280;  // past, up to one tile per CU
+constexpr int64_t kScatterFewRows = 1024;
 
 // Gradient products (fp32 outputs, K = the batch's rows) of at most this depth
 // are mostly their stores too, which 128 x 128 register-staged tiles, two to a
@@ -372,7 +377,8 @@ hipError_t launch_gemm(int site, const T* A, int64_t lda, int64_t M, const T* B,
     constexpr bool kScatter = KM == 0 && (DualEpiT<Epi>::value || ScatterRowsT<Epi>::value);
     const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128);
     const bool staged = kScatter && !(g.bm == 256 && g.bn == 128) &&
-                        (K <= kScatterShortK || (g.bn == 192 && lda % 64 != 0));
+                        (K <= (t128 <= kCus ? kScatterShortK128 : kScatterShortK) ||
+                         (lda % 64 != 0 && (g.bn == 192 || (t128 <= kCus && M <= kScatterFewRows))));
     const bool direct = KM == 0
                             ? !staged
                             : aligned16(A) && aligned16(B) && lda % 8 == 0 && ldb % 8 == 0 &&

@@ -36,12 +36,13 @@ def _bf16(shape, seed):
     (2041, 2040, 200, (128, 128)),
     (1921, 2047, 328, (128, 128)),
     # scattered outputs past the depth up to which the 256 x 256, 256 x 192 and
-    # 128 x 128 tiles go through registers (768), and rows of X that start
-    # inside a line on 256 x 192 tiles
+    # 128 x 128 tiles go through registers (768; 1280 up to one tile per CU),
+    # and rows of X that start inside a line on 256 x 192 tiles and with few rows
     (4095, 4041, 776, (256, 256)),
     (4090, 2500, 832, (256, 192)),
     (4090, 2500, 776, (256, 192)),
-    (1921, 2047, 776, (128, 128)),
+    (1921, 2047, 1288, (128, 128)),
+    (1021, 3847, 1288, (128, 128)),
     # more 128 x 128 tiles than CUs, two to a CU
     (1855, 4120, 136, (128, 128)),
     (1855, 4115, 328, (128, 128)),
