@@ -252,6 +252,7 @@ __device__ __forceinline__ void gemm_dma_tile(const T* __restrict__ A, int64_t l
     constexpr int STAGE = OpA::kBytes + OpB::kBytes;
     constexpr int DPW = OpA::kPieces + OpB::kPieces;  // loads per issuing wave and K tile
     static_assert(NW == 8 && S * STAGE <= 163840, "eight multiplying waves, 160 KB of LDS");
+    static_assert(!InitEpi<Epi>::value || OldEpi<Epi>::value, "starting values are added at the end");
     __shared__ __attribute__((aligned(1024))) char smem[gemm_dma_lds<BM, BN, S>()];
 
     const int64_t m0 = tm * BM, n0 = tn * BN;

@@ -2,8 +2,9 @@
 //
 // Both operands are K-contiguous row-major (A: M x K activations, B: N x K
 // weight rows), which is the layout the MFMA operand registers want: a lane
-// supplies 8 consecutive K values of one row.  Used for X W_p^T (bf16),
-// Y_p C^T (fp16 operands) and the dense / low-rank baselines.
+// supplies 8 consecutive K values of one row.  Used for the products that
+// gemm_dma.hpp does not take: tiles of 64 columns, K splits, shallow products
+// that are mostly stores and K-major operands of unaligned buffers.
 //
 // Block tile BM x BN, K step BK, staged through LDS with double buffering,
 // 8 waves (2 per SIMD) each owning a 64 x 64 sub-tile of 32x32x16 MFMAs.
@@ -38,9 +39,9 @@
 namespace pifa {
 
 // An epilogue with init(m, col) gives the starting value of acc(m, n) (the
-// product is added to it): the GEMM loads it before its K loop, where the
+// product is added to it): this GEMM loads it before its K loop, where the
 // load latency hides behind the first tiles' loads, and split_reduce starts
-// its sum with it.
+// its sum with it (gemm_dma.hpp adds it at the end, see OldEpi).
 template <typename E, typename = void>
 struct InitEpi {
     static constexpr bool value = false;
@@ -507,45 +508,8 @@ __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int64_t ld
     for (int u = 0; u < PGR - 1; ++u)
         if (kt + u < nk) body(kt + u, S[(u + 1) % PGR]);
 
-    // 256 x 128 tiles of the plain bf16 scatter (the non-pivot product) write
-    // their outputs row by row through LDS: each store instruction of a wave
-    // covers 64 consecutive tile columns of one output row, whose scattered
-    // destinations span about two lines of Y, instead of 32 columns of two
-    // rows.  Attention layer at M = 4096, three alternating passes: 47.6-47.9
-    // -> 46.7-47.1 us per launch, bit-identical outputs.  The other tiles keep
-    // the element-wise stores (staged this way the 256 x 192 and 256 x 256
-    // tiles lost 10-15%, and the 128 x 128 tiles of M = 2048 about 0.8 us).
-    constexpr bool kRowScatter = std::is_same<Epi, ScatterEpi<bf16, kWsNone>>::value && BM == 256 && BN == 128 &&
-                                 WM * WN == 8;
-    if constexpr (!kEarlyCols && !kRowScatter) fill_ecols();
-    if constexpr (kRowScatter) {
-        constexpr int P = BN + 8;  // LDS row pitch (elements)
-        static_assert(BM * P * 2 <= LDS_BYTES, "row staging does not fit the tile's LDS");
-        uint16_t* tile = reinterpret_cast<uint16_t*>(smem);
-        const auto c_lo = epi.col(n0 + lane), c_hi = epi.col(n0 + kWave + lane);
-        __syncthreads();  // every wave is done with the operand buffers
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int nl = wn * WTN + j * 32 + (lane & 31);
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int ml = wm * WTM + i * 32 + 4 * (lane >> 5) + 8 * (v >> 2) + (v & 3);
-                    tile[ml * P + nl] = f32_to_bf16_bits(acc[i][j][v] * epi.out_scale);
-                }
-            }
-        __syncthreads();
-        uint16_t* out = reinterpret_cast<uint16_t*>(epi.out);
-        for (int r = wave; r < BM; r += WM * WN) {
-            const int64_t m = m0 + r;
-            if (m >= epi.M) break;
-            const uint16_t lo = tile[r * P + lane], hi = tile[r * P + kWave + lane];
-            if (c_lo.out_ok) out[m * epi.ldo + c_lo.dst] = lo;
-            if (c_hi.out_ok) out[m * epi.ldo + c_hi.dst] = hi;
-        }
-        return;
-    } else if constexpr (StagedEpiT<Epi>::value) {
+    if constexpr (!kEarlyCols) fill_ecols();
+    if constexpr (StagedEpiT<Epi>::value) {
         staged_store<BM, BN, WM, WN, TM, TN>(acc, m0, n0, epi, smem, LDS_BYTES);
         return;
     } else if constexpr (RowsPlusStagedEpiT<Epi>::value) {
@@ -578,22 +542,6 @@ __device__ __forceinline__ void gemm_nt_tile(const T* __restrict__ A, int64_t ld
         }
         staged_store<BM, BN, WM, WN, TM, TN>(acc, m0, n0, epi.ws, smem, LDS_BYTES);
         return;
-    } else if constexpr (Store4Epi<Epi>::value && BM == 256) {
-        // rows outer on the 256-row tiles too (the backward's dX = G_p W_p on
-        // 256 x 256 tiles, three alternating passes: 77.9-78.7 -> 76.3-76.7 us)
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int64_t mb = m0 + wm * WTM + i * 32 + 4 * (lane >> 5);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    const float v4[4] = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2],
-                                         acc[i][j][4 * q + 3]};
-                    epi.store4(mb + 8 * q, ecols[j], v4);
-                }
-            }
-        }
     } else if constexpr (std::is_same<Epi, ScatterEpi<bf16, kWsNone>>::value && BM == 256) {
         // the wider tiles of the non-pivot product: rows outer, so that the
         // stores of one group of rows go out across all column blocks in turn
