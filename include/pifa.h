@@ -93,12 +93,17 @@ pifa_status pifa_validate_partition(const int32_t* pivot_idx, const int32_t* non
  * Host-only diagnostic: the output tile (tile_m x tile_n rows x columns of
  * Y) and the number of K splits (1 = none; otherwise fp32 partial products
  * summed by a second kernel) that a prefill product Y = A B^T of M x N
- * outputs over K runs with (more than 16 activation rows; the products of
- * pifa_forward, the baselines, the backward pass and the calibration sums
- * all take this plan).  wide_epilogue = 0 for epilogues that keep per-output
- * state (fp32 or fp64 outputs, starting values), which never take the 256 x
- * 256 and 256 x 192 tiles.  Needs no GPU.  Returns PIFA_OK or
- * PIFA_ERR_INVALID_ARG (a size below 1 or a null pointer).
+ * outputs over K runs with (more than 16 activation rows).  wide_epilogue:
+ *   2  a product whose operands are K-major, which have no 256 x 192 tile:
+ *      dW_p and dC of the backward pass and the calibration sums of aligned
+ *      rows.  (dW_p and dC over at most 512 rows take 128 x 128 tiles where
+ *      256 x 256 ones need more than one round of the chip.)
+ *   0  the plan without the 256 x 256 and 256 x 192 tiles, for comparison: no
+ *      product takes it;
+ *   any other value: every other product of pifa_forward, the baselines, the
+ *      backward pass and the calibration sums.
+ * Needs no GPU.  Returns PIFA_OK or PIFA_ERR_INVALID_ARG (a size below 1 or a
+ * null pointer).
  */
 pifa_status pifa_gemm_plan(int64_t M, int64_t N, int64_t K, int wide_epilogue, int64_t* tile_m,
                            int64_t* tile_n, int64_t* k_splits);

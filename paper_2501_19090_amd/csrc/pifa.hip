@@ -232,8 +232,9 @@ struct GemmPlan {
     int64_t bm, bn;
     SplitPlan split;
 };
-// Which of the wide tiles a product may take: none (256 x 128 at most), all,
-// or only the square one (K-major operands: their tiles are powers of two).
+// Which of the wide tiles a plan may take: none (256 x 128 at most; no product
+// asks for it, pifa_gemm_plan answers it), all, or only the square one (K-major
+// operands: their tiles are powers of two).
 enum WideTiles : int { kWideNone = 0, kWideAll = 1, kWideSquare = 2 };
 GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, int wide, bool can_split);
 
@@ -999,7 +1000,8 @@ const char* pifa_status_string(pifa_status s) {
 pifa_status pifa_gemm_plan(int64_t M, int64_t N, int64_t K, int wide_epilogue, int64_t* tile_m,
                            int64_t* tile_n, int64_t* k_splits) {
     if (M < 1 || N < 1 || K < 1 || !tile_m || !tile_n || !k_splits) return PIFA_ERR_INVALID_ARG;
-    const GemmPlan g = gemm_plan(M, N, K, wide_epilogue ? kWideAll : kWideNone, true);
+    const int wide = wide_epilogue == kWideNone || wide_epilogue == kWideSquare ? wide_epilogue : kWideAll;
+    const GemmPlan g = gemm_plan(M, N, K, wide, true);
     *tile_m = g.bm;
     *tile_n = g.bn;
     *k_splits = g.split.splits;

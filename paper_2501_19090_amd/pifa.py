@@ -235,11 +235,11 @@ def pifa_status_string(status: int) -> str:
     return lib().pifa_status_string(int(status)).decode()
 
 
-def pifa_gemm_plan(M: int, N: int, K: int, wide_epilogue: bool = True):
+def pifa_gemm_plan(M: int, N: int, K: int, wide_epilogue: int = True):
     """(tile_m, tile_n, k_splits) of a prefill product of M x N outputs over K
     (host only).  Raises on an invalid size."""
     tm, tn, ks = _i64(), _i64(), _i64()
-    _check("pifa_gemm_plan", lib().pifa_gemm_plan(int(M), int(N), int(K), int(bool(wide_epilogue)), ctypes.byref(tm),
+    _check("pifa_gemm_plan", lib().pifa_gemm_plan(int(M), int(N), int(K), int(wide_epilogue or 0), ctypes.byref(tm),
                                                   ctypes.byref(tn), ctypes.byref(ks)))
     return tm.value, tn.value, ks.value
 

@@ -178,6 +178,19 @@ def test_gemm_plan_of_measured_shapes(shape, wide, plan):
     assert pifa.pifa_gemm_plan(*shape, wide_epilogue=wide) == plan
 
 
+def test_gemm_plan_of_k_major_products():
+    """K-major operands have no 256 x 192 tile; where that is not the tile
+    chosen, both plans agree, K splits (which size the partial sums) included."""
+    assert pifa.pifa_gemm_plan(4096, 2496, 4096, wide_epilogue=2) == (256, 256, 1)
+    for M in (17, 100, 128, 640, 1000, 2048, 4096, 11008):
+        for N in (64, 200, 410, 832, 2048, 2496, 4096, 8960):
+            for K in (64, 512, 4096, 16384):
+                all_tiles = pifa.pifa_gemm_plan(M, N, K)
+                square = pifa.pifa_gemm_plan(M, N, K, wide_epilogue=2)
+                assert square[2] == all_tiles[2] and square[:2] != (256, 192)
+                assert square == all_tiles or all_tiles[:2] == (256, 192)
+
+
 def test_gemm_plan_splits_small_batches():
     """Few rows: K is split, over 64 x 64 tiles up to 128 rows and over
     128 x 64 tiles above (half the splits 128 x 128 tiles would need for as
