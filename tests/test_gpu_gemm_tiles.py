@@ -159,14 +159,14 @@ def test_backward_column_split(d_out, r, M, offset):
     torch.cuda.synchronize()
     lay.close()
     Gp = Gd[:, piv] + Gd[:, npiv] @ Cd
-    ref = Gp.T @ Xd
-    # bf16(G_p) feeds dW_p: 2^-9 of each |G_p| |X| term
-    assert np.linalg.norm(dWp.cpu().numpy() - ref) <= 2.0 ** -8 * np.linalg.norm(np.abs(Gp).T @ np.abs(Xd))
+    # bf16(G_p) feeds dW_p, 2^-9 of each of its terms, and dX is rounded to
+    # bf16, 2^-9 of each value: the errors of the terms are independent, so of
+    # the whole gradient no more than twice that is left (test_gpu_backward.py)
+    for got, ref in ((dWp.cpu().numpy(), Gp.T @ Xd), (from_dev(dX), Gp @ Wd)):
+        assert np.linalg.norm(got - ref) <= 5e-3 * np.linalg.norm(ref)
     ref = Gd[:, npiv].T @ Yb.double().numpy()[:, piv]
     bound = (M + 2) * U32 * (np.abs(Gd[:, npiv]).T @ np.abs(Yb.double().numpy()[:, piv]))
     assert np.all(np.abs(dC.cpu().numpy() - ref) <= bound + 1e-30)
-    ref = Gp @ Wd
-    assert np.linalg.norm(from_dev(dX) - ref) <= 2.0 ** -8 * np.linalg.norm(np.abs(Gp) @ np.abs(Wd))
 
 
 @pytest.mark.parametrize("M,N,K", [
