@@ -295,6 +295,9 @@ __global__ __launch_bounds__(256) void transpose64(const double* __restrict__ in
 // of the calibration statistics; fp32 products are accumulated in fp64).
 // With lower_tiles, output tiles entirely above the diagonal are skipped (a
 // symmetric sum; complete_lower64 fills them afterwards).
+// out holds at least kAccF64MinElems values, a run of any tile.
+constexpr int64_t kAccF64MinElems = 32;
+
 struct AccF64Epi {
     double* out;
     int64_t ld, N, M;
@@ -323,9 +326,10 @@ struct AccF64Epi {
     };
     template <int W>
     __device__ __forceinline__ Old<W> old(int64_t m, int64_t n) const {
-        Old<W> o{};
-        if (M * ld < W) return o;  // no run of these sums is whole (the same for every lane)
-        // unconditional, from a valid address, where the run is not whole
+        static_assert(W <= kAccF64MinElems, "run past the smallest sums");
+        Old<W> o;
+        // unconditional, from a valid address, where the run is not whole (the
+        // sums' allocation holds a run; a branch here took 3% of a batch)
         const bool whole = m < M && n + W <= N;
         const f64x2_a8* src = reinterpret_cast<const f64x2_a8*>(out + (whole ? m * ld + n : 0));
 #pragma unroll

@@ -1746,7 +1746,7 @@ pifa_status pifa_calib_create(int64_t d_in, pifa_calib_handle* out) {
     pifa_calib* c = new (std::nothrow) pifa_calib();
     if (!c) return PIFA_ERR_OOM;
     c->n = d_in;
-    const size_t b = (size_t)d_in * d_in * sizeof(double);
+    const size_t b = (size_t)std::max<int64_t>(d_in * d_in, kAccF64MinElems) * sizeof(double);
     if (hipGetDevice(&c->device) != hipSuccess) { free_calib(c); return PIFA_ERR_HIP; }
     if (hipMalloc(&c->S, b) != hipSuccess || hipMalloc(&c->P, b) != hipSuccess ||
         hipMalloc(&c->info, sizeof(int)) != hipSuccess) {
