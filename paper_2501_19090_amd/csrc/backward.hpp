@@ -358,16 +358,9 @@ __global__ __launch_bounds__(256) void rows_to_f16(const float* __restrict__ gp,
     const int64_t m = blockIdx.x;
     const f32x4* row = reinterpret_cast<const f32x4*>(gp + m * n);
     const int64_t nq = n / 4;
-    // a padding column is NaN where the gradient's row holds an infinity (the
-    // product's zero weights times it): as a zero it adds nothing to dX
-    auto load = [&](int64_t q) {
-        f32x4 v = row[q];
-        for (int e = 0; e < 4; ++e) v[e] = 4 * q + e < r ? v[e] : 0.f;
-        return v;
-    };
     float mx = 0.f;
     for (int64_t q = threadIdx.x; q < nq; q += 256) {
-        const f32x4 v = load(q);
+        const f32x4 v = row[q];  // past r: zeros, or NaN, which fmaxf passes over
         mx = fmaxf(mx, fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))));
     }
     for (int off = kWave / 2; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
@@ -383,7 +376,12 @@ __global__ __launch_bounds__(256) void rows_to_f16(const float* __restrict__ gp,
     }
     const float sc = ldexpf(1.f, s);
     for (int64_t q = threadIdx.x; q < nq; q += 256) {
-        const f32x4 v = load(q);
+        f32x4 v = row[q];
+        // a padding column is NaN where the gradient's row holds an infinity
+        // (the product's zero weights times it): as a zero it adds nothing to dX
+        const int left = (int)(r - 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = e < left ? v[e] : 0.f;
         f16 h[4] = {(f16)(v[0] * sc), (f16)(v[1] * sc), (f16)(v[2] * sc), (f16)(v[3] * sc)};
         *reinterpret_cast<uint64_t*>(out + m * n + 4 * q) = __builtin_bit_cast(uint64_t, h);
     }
