@@ -1,4 +1,4 @@
-// Prefill GEMM on CDNA4 matrix cores, 256-row tiles: acc(m, n) = sum_k A[m, k] * B[n, k].
+// Prefill GEMM on CDNA4 matrix cores, tiles of 128 x 128 to 256 x 256: acc(m, n) = sum_k A[m, k] * B[n, k].
 //
 // One workgroup per output tile; K in tiles of 64.  Operand tiles go from
 // memory straight into LDS (buffer_load_dwordx4 ... lds, no registers and no

@@ -327,9 +327,9 @@ void launch_dma(const T* A, int64_t lda, int64_t M, const T* B, int64_t ldb, int
 }
 
 // Products of at most this depth whose epilogue scatters bf16 columns run
-// through registers: their stores are most of the time, and leave sooner from
-// the 32 x 32 accumulators of two workgroups per CU than row by row through
-// LDS.  Direct / register-staged, us, odd rows of outputs: 256 x 192 tiles
+// through registers: their stores are most of the time, and leave sooner
+// element by element from the accumulators than row by row through LDS.
+// Direct / register-staged, us, odd rows of outputs: 256 x 192 tiles
 // (3653 x 6174 x 64) 28.1 / 24.3, (4482 x 2076 x 256) 18.0 / 16.5, (3640 x 2798
 // x 768) 26.2 / 26.1; 256 x 256 tiles (5932 x 4973 x 128) 34.7 / 32.0, (3863 x
 // 7155 x 768) 60.3 / 61.1; up to 256 tiles of 128 x 128 (2885 x 1140 x 256) 9.4
