@@ -7,11 +7,12 @@
 //   dX   = G_p W_p                    (M x d_in)
 //   dW_p = G_p^T X                    (r x d_in)
 //   dC   = G[:, I^c]^T Y_p            (n_np x r)
-// All four are products for the prefill GEMM (gemm_mfma.hpp).  G_p and dX
+// All four are products for the prefill GEMM (gemm_dma.hpp, gemm_mfma.hpp).  G_p and dX
 // take K-contiguous operands; dW_p and dC reduce over the activation rows
 // and read their operands K-major (rows of G_p, X, G[:, I^c], Y[:, I]).  This
-// file holds the gathers of G[:, I^c] and Y[:, I] as rows, the transposed
-// weight packs and the epilogue of the G_p product.
+// file holds the gathers of G[:, I^c], G[:, I] and Y[:, I] as rows, the
+// transposed weight packs and the epilogues of the G_p and dX products (and the
+// transpose that calibration batches of unaligned rows take).
 //
 // Precision: G_p multiplies W_p in dX = G_p W_p with the same cancellation as
 // Y_p C^T in the forward (C rebuilds W_np from W_p): a bf16 G_p misses the
@@ -82,36 +83,27 @@ __global__ void pack_transposed(const TS* __restrict__ src, int64_t src_kb, int6
     }
 }
 
-// One pass over a 64 x 64 tile of in[m][col(j)] (col(j) = idx[j], or j when
-// idx is null), for m < M and j < ncols, written
-//   row-major:  out_r[m * ld_r + j]  (j < ld_r; zero for j >= ncols), and/or
-//   transposed: out_t[j * ld_t + m]  (m < ld_t; zero for m >= M),
-// with 16-byte stores (ld_r, ld_t multiples of 8).  The gathered loads are
-// 2 bytes wide; with sorted indices neighbouring lanes read neighbouring
-// columns of one row.  Grid: (ceil(max(M, ld_t) / 64), ceil(max(ncols, ld_r) / 64)).
+// One pass over a 64 x 64 tile of in (M x n, row stride n), written
+// transposed: out[j * ld + m] for m < ld (zero for m >= M), with 16-byte
+// stores (ld a multiple of 8).  Rows of 16-byte units are read 8 columns per
+// load, others one.  Grid: (ceil(ld / 64), ceil(n / 64)).
 constexpr int kTrTile = 64;
 
-__global__ __launch_bounds__(256) void gather_tile(const bf16* __restrict__ in, int64_t ld_in, int64_t M,
-                                                   const int32_t* __restrict__ idx, int64_t ncols,
-                                                   bf16* __restrict__ out_r, int64_t ld_r, bf16* __restrict__ out_t,
-                                                   int64_t ld_t) {
+__global__ __launch_bounds__(256) void transpose_tile(const bf16* __restrict__ in, int64_t M, int64_t n,
+                                                      bf16* __restrict__ out, int64_t ld) {
     __shared__ uint16_t tile[kTrTile][kTrTile + 2];
     const uint16_t* src = reinterpret_cast<const uint16_t*>(in);
     const int64_t m0 = (int64_t)blockIdx.x * kTrTile, j0 = (int64_t)blockIdx.y * kTrTile;
     const int tid = threadIdx.x;
-    if (!idx && (ld_in & 7) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {
-        // plain transpose of 16-byte aligned rows: 8 columns per load
+    if ((n & 7) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int ch = tid + 256 * i, mm = ch / 8, j8 = (ch % 8) * 8;
             const int64_t m = m0 + mm, j = j0 + j8;
-            uint16_t v[8];
-            if (m < M && j + 8 <= ncols) {
-                const u32x4 w = *reinterpret_cast<const u32x4*>(src + m * ld_in + j);
+            uint16_t v[8] = {};
+            if (m < M && j < n) {
+                const u32x4 w = *reinterpret_cast<const u32x4*>(src + m * n + j);
                 __builtin_memcpy(v, &w, 16);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = (m < M && j + e < ncols) ? src[m * ld_in + j + e] : (uint16_t)0;
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) tile[mm][j8 + e] = v[e];
@@ -122,18 +114,17 @@ __global__ __launch_bounds__(256) void gather_tile(const bf16* __restrict__ in, 
         // memory round trip per element
         const int jj = tid % kTrTile;
         const int64_t j = j0 + jj;
-        const int64_t cj = j < ncols ? (idx ? (int64_t)idx[j] : j) : 0;
         constexpr int kPer = kTrTile * kTrTile / 256;
         uint16_t v[kPer];
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const int64_t m = m0 + tid / kTrTile + 4 * i;
-            v[i] = src[(m < M ? m : M - 1) * ld_in + cj];
+            v[i] = src[(m < M ? m : M - 1) * n + (j < n ? j : 0)];
         }
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             const int mm = tid / kTrTile + 4 * i;
-            tile[mm][jj] = (m0 + mm < M && j < ncols) ? v[i] : (uint16_t)0;
+            tile[mm][jj] = (m0 + mm < M && j < n) ? v[i] : (uint16_t)0;
         }
     }
     __syncthreads();
@@ -141,25 +132,12 @@ __global__ __launch_bounds__(256) void gather_tile(const bf16* __restrict__ in, 
     for (int i = 0; i < 2; ++i) {
         const int ch = tid + 256 * i;  // 512 chunks of 8 elements per tile
         const int a = ch / 8, b8 = (ch % 8) * 8;
-        if (out_r) {  // row m0 + a, columns j0 + b8 .. +7
-            const int64_t m = m0 + a, j = j0 + b8;
-            if (m < M && j < ld_r) {
-                uint16_t v[8];
+        const int64_t j = j0 + a, m = m0 + b8;  // row j of the transpose, columns m .. m + 7
+        if (j < n && m < ld) {
+            uint16_t v[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = tile[a][b8 + e];
-                *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out_r) + m * ld_r + j) =
-                    __builtin_bit_cast(u32x4, v);
-            }
-        }
-        if (out_t) {  // row j0 + a of the transpose, columns m0 + b8 .. +7
-            const int64_t j = j0 + a, m = m0 + b8;
-            if (j < ncols && m < ld_t) {
-                uint16_t v[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = tile[b8 + e][a];
-                *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out_t) + j * ld_t + m) =
-                    __builtin_bit_cast(u32x4, v);
-            }
+            for (int e = 0; e < 8; ++e) v[e] = tile[b8 + e][a];
+            *reinterpret_cast<u32x4*>(reinterpret_cast<uint16_t*>(out) + j * ld + m) = __builtin_bit_cast(u32x4, v);
         }
     }
 }

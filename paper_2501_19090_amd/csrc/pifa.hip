@@ -1477,14 +1477,10 @@ pifa_status prepare_backward(pifa_layer* h) {
     return PIFA_OK;
 }
 
-// gather_tile over all of in's needed tiles (see backward.hpp).
-hipError_t launch_gather(const bf16* in, int64_t ld_in, int64_t M, const int32_t* idx, int64_t ncols, bf16* out_r,
-                         int64_t ld_r, bf16* out_t, int64_t ld_t, hipStream_t st) {
-    const int64_t mx = std::max(M, out_t ? ld_t : (int64_t)0);
-    const int64_t nx = std::max(ncols, out_r ? ld_r : (int64_t)0);
-    if (mx == 0 || nx == 0) return hipSuccess;
-    hipLaunchKernelGGL(gather_tile, dim3((unsigned)ceil_div(mx, kTrTile), (unsigned)ceil_div(nx, kTrTile)), dim3(256),
-                       0, st, in, ld_in, M, idx, ncols, out_r, ld_r, out_t, ld_t);
+// out (n x ld) = the transpose of in (M x n, M <= ld), zeros past M.
+hipError_t launch_transpose(const bf16* in, int64_t M, int64_t n, bf16* out, int64_t ld, hipStream_t st) {
+    hipLaunchKernelGGL(transpose_tile, dim3((unsigned)ceil_div(ld, kTrTile), (unsigned)ceil_div(n, kTrTile)), dim3(256),
+                       0, st, in, M, n, out, ld);
     return hipGetLastError();
 }
 
@@ -1812,10 +1808,8 @@ pifa_status pifa_calib_accumulate(pifa_calib_handle c, const void* X_o, const vo
     float* partials = part ? (float*)((char*)c->ws.ptr + (size_t)(2 * e_t) * 2) : nullptr;
     {
         TimedLaunch timed(kSiteCalibGather, st);
-        if (launch_gather((const bf16*)X_u, n, B, nullptr, n, nullptr, 0, xut, Bp, st) != hipSuccess) return PIFA_ERR_HIP;
-        if (X_o != X_u &&
-            launch_gather((const bf16*)X_o, n, B, nullptr, n, nullptr, 0, xot, Bp, st) != hipSuccess)
-            return PIFA_ERR_HIP;
+        if (launch_transpose((const bf16*)X_u, B, n, xut, Bp, st) != hipSuccess) return PIFA_ERR_HIP;
+        if (X_o != X_u && launch_transpose((const bf16*)X_o, B, n, xot, Bp, st) != hipSuccess) return PIFA_ERR_HIP;
     }
     const bf16* xo = X_o == X_u ? xut : xot;
     // S += X_u^T X_u and P += X_o^T X_u: rows of the transposed batches, K = tokens
